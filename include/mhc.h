@@ -11,6 +11,11 @@
  * per trajectory and per object (Sec. IV-D). A scene goes in, criticalities
  * come out (the paper's input / output boxes of Fig. 1, Sec. V).
  *
+ * Pose pairs are decided one step of one trajectory pair at a time by the
+ * overlap test, or many together where the bounds of two groups of trajectories
+ * lie apart at a step by more than the test's rounding; every result is the one
+ * that testing each pose pair gives.
+ *
  * Conventions shared by every entry point
  *   - All functions return an mhc_status; negative values are errors and
  *     mhc_last_error(ctx) then holds a message owned by the context, valid
@@ -334,10 +339,9 @@ mhc_status mhc_tune_load(mhc_ctx *ctx, const char *path);
 /* ---- collision plan check (host only) ----------------------------------- */
 
 /* The collision work of n scenes is cut into units (a wave's items of one
- * object pair: row-major runs of the pair's item grid, or 2-D blocks of it)
- * that the host deals to the waves of the collision kernel (Sec. IV-C: every
- * trajectory of one object against every trajectory of another, at every
- * step). mhc_plan_check builds the plan the library would launch for tile
+ * object pair: a 2-D block of the pair's item grid) that are dealt to the
+ * waves of the collision kernel (Sec. IV-C: every trajectory of one object
+ * against every trajectory of another, at every step). mhc_plan_check builds the plan the library would launch for tile
  * variant `variant` (0 .. MHC_N_VARIANTS-1) with `max_waves` resident waves
  * (0: one wave per unit) and walks it on the host the way the kernel decodes
  * it. It needs no GPU. MHC_OK when every trajectory pair of every object pair
@@ -347,13 +351,13 @@ mhc_status mhc_tune_load(mhc_ctx *ctx, const char *path);
  * check (info filled). */
 typedef struct {
     int64_t n_units;        /* collision units of the plan */
-    int64_t n_waves;        /* wave slots the units are dealt to */
+    int64_t n_waves;        /* waves the blocks of units are dealt to */
     int64_t blocked_pairs;  /* object pairs whose units are 2-D blocks of items */
     int64_t uncovered;      /* items tested by no thread (0 when the plan is sound) */
     int64_t repeated;       /* items tested more than once (0 when sound) */
     int64_t out_of_range;   /* threads deriving an index outside their pair (0 when sound) */
-    int32_t contiguous;     /* 1: waves take contiguous stretches of the unit sequence */
-    int32_t time_split;     /* largest number of step ranges a unit is cut into (1, 2, 4 or 8) */
+    int32_t contiguous;     /* 1: waves go through several blocks of units in turn */
+    int32_t time_split;     /* largest number of steps a unit runs side by side (1, 2, 4 or 8) */
 } mhc_plan_info;
 mhc_status mhc_plan_check(int32_t n_scenes, const mhc_scene *scenes, int32_t variant, int32_t max_waves,
                           mhc_plan_info *info);

@@ -4,6 +4,7 @@
 // street data processing, run in that order, each data-parallel inside).
 #include "mhc_internal.h"
 
+#include <algorithm>
 #include <climits>
 #include <math.h>
 #include <mutex>
@@ -33,7 +34,11 @@ namespace mhc {
 // from one 64-step chunk to the next. Pedestrians (Sec. IV-B.3) move by the
 // constant displacement of their speed and heading each step.
 // Poses are stored as FP32: float4 (x, y, cos psi, sin psi) for vehicles,
-// float2 (x, y) for pedestrians, layout [t][i], slot t = step t+1.
+// float2 (x, y) for pedestrians, layout [t][position], slot t = step t+1. An
+// object's trajectories sit in the order of traj_at, which keeps neighbours
+// of the control grid together; every LEAF of them (one workgroup) gets the
+// box of its positions at every step, from which the collision kernel tells
+// which steps of a block of trajectory pairs can hold an overlap at all.
 // ===========================================================================
 
 // The integer summand of one colliding combination of probability p: p itself
@@ -87,17 +92,32 @@ __device__ __forceinline__ double scan_add(double v, int lane)
     return v;
 }
 
+// The same of an int.
+__device__ __forceinline__ int scan_add_int(int v)
+{
+#define MHC_SCAN_STEP(CTRL, ROWS) v += __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xF, false)
+    MHC_SCAN_STEP(kDppRowShr1, 0xF);
+    MHC_SCAN_STEP(kDppRowShr2, 0xF);
+    MHC_SCAN_STEP(kDppRowShr4, 0xF);
+    MHC_SCAN_STEP(kDppRowShr8, 0xF);
+    MHC_SCAN_STEP(kDppRowBcast15, 0xA);
+    MHC_SCAN_STEP(kDppRowBcast31, 0xC);
+#undef MHC_SCAN_STEP
+    return v;
+}
+
 // The value of the lane below (lane 0 gets `first`).
 __device__ __forceinline__ double lane_below(double x, double first) { return dpp_move<kDppWaveShr1, 0xF>(x, first); }
 
-// The sum of v over a workgroup of WG threads, in a fixed order: each wave's
-// sum by the DPP scan (its lane 63), then the waves' sums in wave order. Every
-// thread of the workgroup must call it; the result is valid in every thread.
+// The sum of v over the first WG threads of a workgroup, in a fixed order: each
+// wave's sum by the DPP scan (its lane 63), then the waves' sums in wave order.
+// Every thread of the workgroup must call it; the result is valid in every
+// thread.
 __device__ __forceinline__ double block_sum(double v, double *ws)
 {
     const int lane = (int)(threadIdx.x & (WAVE - 1)), w = (int)(threadIdx.x / WAVE);
     v = scan_add(v, lane);
-    if (lane == WAVE - 1) ws[w] = v;
+    if (lane == WAVE - 1 && w < WG / WAVE) ws[w] = v;
     __syncthreads();
     double s = ws[0];
 #pragma unroll
@@ -105,7 +125,7 @@ __device__ __forceinline__ double block_sum(double v, double *ws)
     return s;
 }
 
-// Thread tid adds the scores tid, tid + 256, ... in ascending order, eight
+// Thread tid < 256 adds the scores tid, tid + 256, ... in ascending order, eight
 // loads in flight at a time, then the workgroup adds the 256 partial sums in a
 // fixed order (block_sum): the order depends on T only.
 __device__ void normalise_probabilities(const DObj &o, int obj, const double *__restrict__ vals,
@@ -116,7 +136,7 @@ __device__ void normalise_probabilities(const DObj &o, int obj, const double *__
     const int tid = threadIdx.x;
     const double *__restrict__ sc = vals + o.score_off;
     double part = 0.0;
-    if (o.has_score) {
+    if (o.score_off >= 0 && tid < WG) {
         for (int base = 0; base < o.T; base += 8 * WG) {
             double v[8];
 #pragma unroll
@@ -130,18 +150,19 @@ __device__ void normalise_probabilities(const DObj &o, int obj, const double *__
         }
     }
     const double total = block_sum(part, red);
+    if (tid >= WG) return;
     for (int base = 0; base < o.T; base += 8 * WG) {
         double v[8];
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
             const int idx = base + k * WG + tid;
-            v[k] = (o.has_score && idx < o.T) ? sc[idx] : 0.0;
+            v[k] = (o.score_off >= 0 && idx < o.T) ? sc[idx] : 0.0;
         }
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
             const int idx = base + k * WG + tid;
             if (idx < o.T) {
-                const double pk = o.has_score ? v[k] / total : 1.0 / (double)o.T;
+                const double pk = o.score_off >= 0 ? v[k] / total : 1.0 / (double)o.T;
                 p[o.traj_off + idx] = pk;
                 pfix[o.traj_off + idx] = fixed_term(o.risk, pk);
             }
@@ -152,22 +173,60 @@ __device__ void normalise_probabilities(const DObj &o, int obj, const double *__
     if (tid == 0) done[obj] = 0ull;
 }
 
-// A vehicle pose (x, y, cos, sin) in its own frame: K = (x cos + y sin,
-// y cos - x sin) is its centre there, and (K_x, K_y, cos, sin) is what the
-// rectangle tests take for the rectangle they measure in its frame. The
-// trajectory kernel writes it beside the pose (the object's frame block), in
-// FP32 from the stored FP32 pose, so that no test prepares it again.
-__device__ __forceinline__ float4 rect_frame(const float4 P)
+// The box that a leaf's shapes cover at one step, as (x_min, x_max, y_min,
+// y_max): the bounds of each trajectory's shape at its pose, of half length hl
+// along the heading and half width hw across it (circles: the radius in both).
+// A pose that an overlap test could not be trusted to separate (not finite, or
+// so far out that its products overflow) makes the box infinite, so that no
+// test of the leaf is left out at that step.
+__device__ __forceinline__ float4 box_none() { return make_float4(INFINITY, -INFINITY, INFINITY, -INFINITY); }
+
+__device__ __forceinline__ float4 box_join(const float4 a, const float4 b)
 {
-    return make_float4(fmaf(P.x, P.z, P.y * P.w), fmaf(P.y, P.z, -(P.x * P.w)), P.z, P.w);
+    return make_float4(fminf(a.x, b.x), fmaxf(a.y, b.y), fminf(a.z, b.z), fmaxf(a.w, b.w));
 }
 
-// Stores vehicle pose n of trajectory i and its frame form.
-__device__ __forceinline__ void store_vehicle_pose(char *__restrict__ poses, const DObj &o, int n, int i, const float4 P)
+__device__ __forceinline__ float4 box_of(float x, float y, float c, float s, float hl, float hw)
 {
-    const size_t k = (size_t)n * o.T + i;
-    reinterpret_cast<float4 *>(poses + o.pose_off)[k] = P;
-    reinterpret_cast<float4 *>(poses + o.frame_off)[k] = rect_frame(P);
+    const bool ok = (fabsf(x) <= kBoxMax) & (fabsf(y) <= kBoxMax) & (fabsf(c) <= 2.0f) & (fabsf(s) <= 2.0f);
+    const float hx = fmaf(hl, fabsf(c), hw * fabsf(s)), hy = fmaf(hl, fabsf(s), hw * fabsf(c));
+    return ok ? make_float4(x - hx, x + hx, y - hy, y + hy) : make_float4(-INFINITY, INFINITY, -INFINITY, INFINITY);
+}
+
+// Writes the boxes of the workgroup's leaf for steps n0 .. n0 + 63: every wave
+// brings the box of its trajectory's pose at step n0 + lane (box_none where it
+// has none), the first wave joins them. Every thread of the workgroup calls it.
+__device__ __forceinline__ void store_leaf_boxes(char *__restrict__ poses, const DObj &o, int leaf, int n0, float4 mine)
+{
+    __shared__ float4 box[2][LEAF][WAVE];
+    const int lane = (int)(threadIdx.x & (WAVE - 1)), w = (int)(threadIdx.x / WAVE);
+    const int buf = (n0 / WAVE) & 1;   // the next chunk's boxes may be written while these are read
+    box[buf][w][lane] = mine;
+    __syncthreads();
+    if (w == 0 && n0 + lane < o.H) {
+        float4 b = box[buf][0][lane];
+#pragma unroll
+        for (int k = 1; k < LEAF; ++k) b = box_join(b, box[buf][k][lane]);
+        reinterpret_cast<float4 *>(poses + o.box_off)[(size_t)leaf * o.H + n0 + lane] = b;
+    }
+}
+
+// Workgroup wg of n_wg writes its share of -1 (no collision) over the n
+// first-hit entries: the collision kernel stores colliding pairs only.
+__device__ __forceinline__ void clear_hits(int16_t *__restrict__ hits, int64_t n, int64_t wg, int64_t n_wg)
+{
+    // entries before the first 16-byte boundary, 16-byte stores, the rest
+    const int64_t head = min(n, (int64_t)((16 - (reinterpret_cast<uintptr_t>(hits) & 15)) & 15) / 2);
+    const int64_t wide = (n - head) / 8;
+    const int64_t per = (wide + n_wg - 1) / n_wg;
+    const int64_t k1 = min(wide, (wg + 1) * per);
+    uint4 *h16 = reinterpret_cast<uint4 *>(hits + head);
+    for (int64_t k = wg * per + threadIdx.x; k < k1; k += blockDim.x) h16[k] = make_uint4(~0u, ~0u, ~0u, ~0u);
+    if (wg == 0) {
+        const int t = (int)threadIdx.x;
+        if (t < head) hits[t] = -1;
+        if (head + wide * 8 + t < n && t < 8) hits[head + wide * 8 + t] = -1;
+    }
 }
 
 // Vehicle trajectory i on the linear one-track model (Sec. IV-B.1): side slip
@@ -181,7 +240,7 @@ __device__ __forceinline__ void store_vehicle_pose(char *__restrict__ poses, con
 // conditions) the lateral state takes the steady state at v_{n+1} instead:
 //   r = v delta / (L (1 + K v^2)), beta = delta (lr/L - m lf v^2/(cr L^2)) / (1 + K v^2),
 // L = lf + lr, K = m (lr cr - lf cf) / (L^2 cf cr). FP64; poses stored as
-// FP32 (x, y, cos psi, sin psi), [t][i].
+// FP32 (x, y, cos psi, sin psi), [t][position].
 //
 // Evaluation: one wave per trajectory, a lane per step, chunks of 64 steps
 // with the state carried across chunks. The speed has a closed form,
@@ -196,7 +255,7 @@ __device__ __forceinline__ void store_vehicle_pose(char *__restrict__ poses, con
 
 
 __device__ void one_track_wave(const DObj &o, const double *__restrict__ vals, char *__restrict__ poses, int i,
-                               int lane)
+                               int pos, int leaf, bool exists, int lane)
 {
     const double cf = o.params[0], cr = o.params[1], lf = o.params[2], lr = o.params[3];
     const double m = o.params[4], Iz = o.params[5];
@@ -217,7 +276,7 @@ __device__ void one_track_wave(const DObj &o, const double *__restrict__ vals, c
     sincos(cpsi, &csp, &ccp);
     for (int n0 = 0; n0 < o.H; n0 += 64) {
         const int n = n0 + lane;
-        const bool active = n < o.H;
+        const bool active = n < o.H && exists;
         const double v = fmax(o.speed + (double)n * at, 0.0);
         double vdot = accel, v1 = v + at;
         if (v1 < 0.0) {
@@ -297,7 +356,9 @@ __device__ void one_track_wave(const DObj &o, const double *__restrict__ vals, c
         const double ay = sb * vdot + cb * v * (beta_dot + r);
         const double x1 = cx + scan_add(active ? cpb * v * tau + cp * ax * h2 - sp * ay * h2 : 0.0, lane);
         const double y1 = cy + scan_add(active ? spb * v * tau + sp * ax * h2 + cp * ay * h2 : 0.0, lane);
-        if (active) store_vehicle_pose(poses, o, n, i, make_float4((float)x1, (float)y1, (float)cp1, (float)sp1));
+        const float4 P = make_float4((float)x1, (float)y1, (float)cp1, (float)sp1);
+        if (active) reinterpret_cast<float4 *>(poses + o.pose_off)[(size_t)n * o.T + pos] = P;
+        if (o.box_off >= 0) store_leaf_boxes(poses, o, leaf, n0, active ? box_of(P.x, P.y, P.z, P.w, o.hl, o.hw) : box_none());
         cx = __shfl(x1, 63, 64);
         cy = __shfl(y1, 63, 64);
         cpsi = __shfl(psi1, 63, 64);
@@ -316,14 +377,17 @@ __device__ void one_track_wave(const DObj &o, const double *__restrict__ vals, c
 // instance's); launches without one-track vehicles use the lighter instance,
 // which also fits beside a running collision kernel on a shared GPU.
 // For time-resolved scenes, trajectory block c also zeroes the c-th stretch
-// of K1_TPB * W * H entries of the object's per-slot q sums.
+// of K1_TPB * W * H entries of the object's per-slot q sums. Where the launch
+// asks for first hits, every workgroup writes its share of -1 over them.
 template <bool ONE_TRACK>
-__global__ __launch_bounds__(WG) void k1_trajgen(const DObj *__restrict__ objs, const double *__restrict__ vals,
+__global__ __launch_bounds__(K1_WG) void k1_trajgen(const DObj *__restrict__ objs, const double *__restrict__ vals,
                                                  char *__restrict__ poses, double *__restrict__ p,
                                                  unsigned long long *__restrict__ pfix,
                                                  unsigned long long *__restrict__ qacc, unsigned long long *__restrict__ done,
-                                                 unsigned long long *__restrict__ hist, const int2 *__restrict__ rows)
+                                                 unsigned long long *__restrict__ hist, const int2 *__restrict__ rows,
+                                                 int16_t *__restrict__ hits, int64_t n_hits)
 {
+    if (hits) clear_hits(hits, n_hits, (int64_t)blockIdx.y * gridDim.x + blockIdx.x, (int64_t)gridDim.x * gridDim.y);
     // the row's object and the block of that object this workgroup is
     int obj = (int)blockIdx.y, xb = (int)blockIdx.x;
     if (rows) {
@@ -343,16 +407,22 @@ __global__ __launch_bounds__(WG) void k1_trajgen(const DObj *__restrict__ objs, 
         const int64_t hi = min(total, lo + per);
         // 16-byte stores: hist_off, the stretch and the total are even
         ulonglong2 *h2 = reinterpret_cast<ulonglong2 *>(hist + o.hist_off);
-        for (int64_t k = lo / 2 + (int64_t)threadIdx.x; k < hi / 2; k += WG) h2[k] = make_ulonglong2(0ull, 0ull);
+        for (int64_t k = lo / 2 + (int64_t)threadIdx.x; k < hi / 2; k += K1_WG) h2[k] = make_ulonglong2(0ull, 0ull);
     }
     const int lane = threadIdx.x & 63;
-    const int i = (xb - 1) * K1_TPB + (int)(threadIdx.x >> 6);
-    if (i >= o.T) return;  // whole wave
+    const int leaf = xb - 1;
+    if (leaf * LEAF >= o.T) return;  // whole workgroup
+    // the trajectory of this wave's position; a wave past the last one keeps
+    // step with the workgroup and writes nothing
+    const int pos = leaf * LEAF + (int)(threadIdx.x >> 6);
+    const bool exists = pos < o.T;
+    const int i = traj_at(min(pos, o.T - 1), o.n_u, o.n_w, o.strip);
     // this trajectory's row of the integer q accumulators starts from zero
-    for (int k = lane; k < o.n_scene_obj; k += 64) qacc[o.q_row + (int64_t)i * o.n_scene_obj + k] = 0ull;
+    if (exists)
+        for (int k = lane; k < o.n_scene_obj; k += 64) qacc[o.q_row + (int64_t)i * o.n_scene_obj + k] = 0ull;
     if constexpr (ONE_TRACK) {
         if (o.model == MODEL_ONE_TRACK) {
-            one_track_wave(o, vals, poses, i, lane);
+            one_track_wave(o, vals, poses, i, pos, leaf, exists, lane);
             return;
         }
     }
@@ -374,9 +444,9 @@ __global__ __launch_bounds__(WG) void k1_trajgen(const DObj *__restrict__ objs, 
     double cx = o.x, cy = o.y;
     for (int n0 = 0; n0 < H; n0 += 64) {
         const int n = n0 + lane;
-        const bool active = n < H;
+        const bool active = n < H && exists;
         double dx = 0.0, dy = 0.0;
-        float c_next = 0.f, s_next = 0.f;
+        float c_next = 1.f, s_next = 0.f;   // circles: bounds hl by hw
         if (active) {
             if (vehicle) {
                 const double wt = w * tau;
@@ -416,11 +486,14 @@ __global__ __launch_bounds__(WG) void k1_trajgen(const DObj *__restrict__ objs, 
         dy = scan_add(dy, lane);
         const double x = cx + dx, y = cy + dy;
         if (active) {
+            const size_t k = (size_t)n * o.T + pos;
             if (vehicle)
-                store_vehicle_pose(poses, o, n, i, make_float4((float)x, (float)y, c_next, s_next));
+                reinterpret_cast<float4 *>(poses + o.pose_off)[k] = make_float4((float)x, (float)y, c_next, s_next);
             else
-                reinterpret_cast<float2 *>(poses + o.pose_off)[(size_t)n * o.T + i] = make_float2((float)x, (float)y);
+                reinterpret_cast<float2 *>(poses + o.pose_off)[k] = make_float2((float)x, (float)y);
         }
+        if (o.box_off >= 0)
+            store_leaf_boxes(poses, o, leaf, n0, active ? box_of((float)x, (float)y, c_next, s_next, o.hl, o.hw) : box_none());
         cx = __shfl(x, 63, 64);
         cy = __shfl(y, 63, 64);
     }
@@ -429,11 +502,16 @@ __global__ __launch_bounds__(WG) void k1_trajgen(const DObj *__restrict__ objs, 
 // ===========================================================================
 // K2: collision recognition (Sec. IV-C).
 //
-// Every trajectory pair of every object pair is tested at every step. A
-// thread owns an RI x RJ micro-tile of trajectory pairs, walks the steps from
-// the last to the first and records the step of each overlap, so the value
-// left at the end is the earliest colliding step (or -1). Tests are exact
-// closed-shape tests in FP32:
+// Every trajectory pair of every object pair is decided at every step. A wave
+// takes a unit: item rows by item columns of one object pair, an
+// item being an RI x RJ micro-tile of trajectory pairs (of neighbouring
+// positions). It first forms, lane l for step l, the boxes of the unit's two
+// groups of trajectories from their leaves' boxes; at a step where the boxes
+// lie further apart than the two shapes reach, no pair of the unit overlaps.
+// The steps left over are walked from the last to the first, each lane testing
+// its micro-tile and recording the step of each overlap, so the value left at
+// the end is the earliest colliding step (or -1). Tests are exact closed-shape
+// tests in FP32:
 //   rectangle-rectangle: separating axes u_P, v_P, u_Q, v_Q; the projected
 //     half extents use |cos(psi_Q - psi_P)| and |sin(psi_Q - psi_P)|;
 //   rectangle-circle: distance from the centre to the rectangle <= r;
@@ -443,17 +521,38 @@ __global__ __launch_bounds__(WG) void k1_trajgen(const DObj *__restrict__ objs, 
 // ===========================================================================
 
 
+// A vehicle pose (x, y, cos, sin) in its own frame: K = (x cos + y sin,
+// y cos - x sin) is its centre there, and (K_x, K_y, cos, sin) is what the
+// rectangle tests take for the rectangle they measure in its frame.
+__device__ __forceinline__ float4 rect_frame(const float4 P)
+{
+    return make_float4(fmaf(P.x, P.z, P.y * P.w), fmaf(P.y, P.z, -(P.x * P.w)), P.z, P.w);
+}
+
+// Which pose a test takes in its own frame: neither, a's or b's.
+struct PrepNone {
+    template <class P> __device__ static __forceinline__ P prep_a(const P p) { return p; }
+    template <class P> __device__ static __forceinline__ P prep_b(const P p) { return p; }
+};
+struct PrepA : PrepNone {
+    __device__ static __forceinline__ float4 prep_a(const float4 p) { return rect_frame(p); }
+};
+struct PrepB : PrepNone {
+    __device__ static __forceinline__ float4 prep_b(const float4 p) { return rect_frame(p); }
+};
+
 // Rectangle-rectangle (separating axes). With C = u_P.u_Q and S = v_P.u_Q
 // (so u_P = C u_Q - S v_Q, v_P = S u_Q + C v_Q) and d = c_Q - c_P, the
 // rectangles overlap iff
 //   |d.u_P| <= lP + lQ|C| + wQ|S|,   |d.v_P| <= wP + lQ|S| + wQ|C|,
 //   |d.u_Q| <= lQ + lP|C| + wP|S|,   |d.v_Q| <= wQ + lP|S| + wP|C|.
-// Q's pose comes in its own frame (its object's frame block: K = c_Q there),
-// so d.u_Q = K.x - (x_P cos_Q + y_P sin_Q) and d.v_Q = K.y - (y_P cos_Q - x_P
+// Q's pose comes in its own frame (rect_frame: K = c_Q there, formed once per
+// pose and step), so d.u_Q = K.x - (x_P cos_Q + y_P sin_Q) and d.v_Q = K.y - (y_P cos_Q - x_P
 // sin_Q) are two FMA chains each, and d.u_P, d.v_P follow from them by the
 // rotation (C, S): 25 VALU per test.
-struct CheckVV {
+struct CheckVV : PrepB {
     float lP, wP, lQ, wQ;
+    __device__ __forceinline__ CheckVV(const DPair &p) : lP(p.la), wP(p.wa), lQ(p.lb), wQ(p.wb) {}
     __device__ __forceinline__ bool operator()(const float4 P, const float4 Qk) const
     {
         const float C = fmaf(P.z, Qk.z, P.w * Qk.w);    // u_P . u_Q = v_P . v_Q
@@ -480,8 +579,9 @@ struct CheckVV {
 // they are (d.u_Q + al*lP*C + be*wP*S, d.v_Q - al*lP*S + be*wP*C).
 // Q's pose comes in its own frame and the projections are formed as in the
 // separating-axes test.
-struct CheckVVPip {
+struct CheckVVPip : PrepB {
     float lP, wP, lQ, wQ;
+    __device__ __forceinline__ CheckVVPip(const DPair &p) : lP(p.la), wP(p.wa), lQ(p.lb), wQ(p.wb) {}
     __device__ __forceinline__ bool operator()(const float4 P, const float4 Qk) const
     {
         const float C = fmaf(P.z, Qk.z, P.w * Qk.w);
@@ -513,8 +613,7 @@ struct CheckVVPip {
 // Rectangle-circle: the circle centre Q in P's frame is (lam, mu) =
 // ((Q - c_P) . u_P, (Q - c_P) . v_P), and the two overlap iff the distance
 // from Q to the rectangle, sqrt(max(|lam| - l, 0)^2 + max(|mu| - w, 0)^2), is
-// at most r. The rectangle's pose comes in its own frame (its object's frame
-// block): K = (x_P cos + y_P sin, y_P cos - x_P sin) is c_P there, so
+// at most r. The rectangle's pose comes in its own frame (rect_frame): K = (x_P cos + y_P sin, y_P cos - x_P sin) is c_P there, so
 //   (lam, mu) = (x_Q cos + y_Q sin - K.x, y_Q cos - x_Q sin - K.y)
 // (two FMA chains each) without the difference Q - c_P: 12 VALU per test.
 // Every tile computes each test with the same operations, so results do not
@@ -528,18 +627,21 @@ __device__ __forceinline__ bool rect_circle(const float4 Pk, const float2 Q, flo
     return fmaf(ex, ex, ey * ey) <= rr;
 }
 
-struct CheckVP {  // a: the rectangle, in its own frame
+struct CheckVP : PrepA {  // a: the rectangle, in its own frame
     float lP, wP, rr;
+    __device__ __forceinline__ CheckVP(const DPair &p) : lP(p.la), wP(p.wa), rr(p.rr) {}
     __device__ __forceinline__ bool operator()(const float4 Pk, const float2 Q) const { return rect_circle(Pk, Q, lP, wP, rr); }
 };
 
-struct CheckPV {  // b: the rectangle, in its own frame
+struct CheckPV : PrepB {  // b: the rectangle, in its own frame
     float lQ, wQ, rr;
+    __device__ __forceinline__ CheckPV(const DPair &p) : lQ(p.lb), wQ(p.wb), rr(p.rr) {}
     __device__ __forceinline__ bool operator()(const float2 P, const float4 Qk) const { return rect_circle(Qk, P, lQ, wQ, rr); }
 };
 
-struct CheckPP {
+struct CheckPP : PrepNone {
     float rr;
+    __device__ __forceinline__ CheckPP(const DPair &p) : rr(p.rr) {}
     __device__ __forceinline__ bool operator()(const float2 P, const float2 Q) const
     {
         const float dx = Q.x - P.x;
@@ -562,8 +664,9 @@ struct CheckPP {
 // the loops are straight-line code; their constants are read from the wave's
 // copy of the two polygons in LDS.
 template <int KP, int KQ, bool PIPMODE>
-struct CheckGG {
+struct CheckGG : PrepNone {
     const DPoly *P, *Q;   // LDS
+    __device__ __forceinline__ CheckGG(const DPoly *p, const DPoly *q) : P(p), Q(q) {}
     __device__ __forceinline__ bool operator()(const float4 a, const float4 b) const
     {
         const float dx = b.x - a.x;
@@ -587,7 +690,7 @@ struct CheckGG {
         }
         if constexpr (!PIPMODE) {
             bool sep = false;
-#pragma unroll
+#pragma unroll 1
             for (int e = 0; e < KP; ++e) {
                 const float nx = P->nx[e], ny = P->ny[e], h = P->h[e];
                 bool out = true;
@@ -595,7 +698,7 @@ struct CheckGG {
                 for (int v = 0; v < KQ; ++v) out &= fmaf(nx, qx[v], ny * qy[v]) > h;
                 sep |= out;
             }
-#pragma unroll
+#pragma unroll 1
             for (int e = 0; e < KQ; ++e) {
                 const float nx = Q->nx[e], ny = Q->ny[e], h = Q->h[e];
                 bool out = true;
@@ -610,13 +713,13 @@ struct CheckGG {
             for (int v = 0; v < KQ; ++v) in_q[v] = true;
 #pragma unroll
             for (int v = 0; v < KP; ++v) in_p[v] = true;
-#pragma unroll
+#pragma unroll 1
             for (int e = 0; e < KP; ++e) {
                 const float nx = P->nx[e], ny = P->ny[e], h = P->h[e];
 #pragma unroll
                 for (int v = 0; v < KQ; ++v) in_q[v] &= fmaf(nx, qx[v], ny * qy[v]) <= h;
             }
-#pragma unroll
+#pragma unroll 1
             for (int e = 0; e < KQ; ++e) {
                 const float nx = Q->nx[e], ny = Q->ny[e], h = Q->h[e];
 #pragma unroll
@@ -644,7 +747,7 @@ __device__ __forceinline__ bool poly_circle(const float4 P, const float2 c, cons
     const float mu = fmaf(dy, P.z, -(dx * P.w));
     bool inside = true;
     float best = 3.0e38f;
-#pragma unroll
+#pragma unroll 1
     for (int e = 0; e < K; ++e) {
         inside &= fmaf(G->nx[e], lam, G->ny[e] * mu) <= G->h[e];
         const float ax = lam - G->vx[e], ay = mu - G->vy[e];
@@ -656,16 +759,18 @@ __device__ __forceinline__ bool poly_circle(const float4 P, const float2 c, cons
 }
 
 template <int K>
-struct CheckGC {
+struct CheckGC : PrepNone {
     const DPoly *G;   // LDS
     float rr;
+    __device__ __forceinline__ CheckGC(const DPoly *g, float r2) : G(g), rr(r2) {}
     __device__ __forceinline__ bool operator()(const float4 P, const float2 Q) const { return poly_circle<K>(P, Q, G, rr); }
 };
 
 template <int K>
-struct CheckCG {
+struct CheckCG : PrepNone {
     const DPoly *G;   // LDS
     float rr;
+    __device__ __forceinline__ CheckCG(const DPoly *g, float r2) : G(g), rr(r2) {}
     __device__ __forceinline__ bool operator()(const float2 P, const float4 Q) const { return poly_circle<K>(Q, P, G, rr); }
 };
 
@@ -690,241 +795,145 @@ __device__ __forceinline__ float2 load_pose<float2>(__amdgpu_buffer_rsrc_t r, ui
     return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, (int)voff, (int)soff, 0));
 }
 
-// The minimum of v over the lanes l ^ E, l ^ 2E, ... (E = 64 >> tshift, the
-// lanes of one item's parts), moved without LDS: lane l ^ 8 by a rotation of
-// its row of 16 by 8 (DPP row_ror), l ^ 16 and l ^ 32 by the gfx950 lane-half
-// swaps, whose two results hold each lane's own value and its partner's.
-__device__ __forceinline__ int min_over_parts(int v, int tshift)
+// When a step needs no tests: the boxes of two groups of trajectories lie apart
+// at that step, along x or along y, by more than the rounding of the tests.
+//
+// That no test of such a step finds an overlap holds for the FP32 tests as
+// they are computed, not only for the shapes: two shapes whose bounds lie m
+// apart are separated by at least 0.38 m along one of the edge normals the
+// tests use (neighbouring edge normals of a Minkowski sum of outlines with
+// interior angles of at least 45 degrees turn by at most 135 degrees;
+// rectangles: 0.7 m), the boxes' and the tests' projections are off by less
+// than 64 half-ulps of the largest coordinate, and m is 256 of them
+// (kBoxSlack). Boxes with an infinite side separate nothing, and the
+// comparison is made so that a NaN keeps the step.
+__device__ __forceinline__ float box_size(const float4 a)
 {
-    if (tshift >= 3) v = min(v, __builtin_amdgcn_update_dpp(v, v, 0x128, 0xF, 0xF, false));
-    if (tshift >= 2) {
-        const auto h = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-        v = min((int)h[0], (int)h[1]);
-    }
-    const auto w = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-    return min((int)w[0], (int)w[1]);
+    return fmaxf(fmaxf(fabsf(a.x), fabsf(a.y)), fmaxf(fabsf(a.z), fabsf(a.w)));
 }
 
-// STAGE: the instance stages the poses of 8 x 8 item blocks in LDS (units of
-// 2-D blocks without a time split): per step, the wave loads each distinct
-// pose of its block once (lane k the k-th pose of either object) into LDS,
-// and every lane then reads its tile's poses from there. The tests and
-// their results are those of the unstaged loop; only where the poses come
-// from differs. Each step's loads are issued before the previous step's tests.
-template <int RI, int RJ, bool TL, class PA, class PB, class Check, bool STAGE = false>
-__device__ __forceinline__ void collide_items(const DPair &pr, int item0, const char *__restrict__ poses,
-                                              int16_t *__restrict__ hits, const unsigned long long *__restrict__ pfix,
-                                              unsigned long long *__restrict__ qacc,
-                                              unsigned long long *__restrict__ hist, const Check chk)
+// size: the larger box_size of the two.
+__device__ __forceinline__ bool boxes_meet(const float4 a, const float4 b, float size)
 {
-    const int n_ig = pr.n_ig, n_jg = pr.n_jg;
-    // time split: E = 64 >> tshift items per unit; part p of the steps per
-    // lane, chunk = ceil(H / S) steps from min(p * chunk, H - chunk), so the
-    // last part ends at H (overlapping its neighbour when S does not divide H)
+    const float gx = fmaxf(b.x - a.y, a.x - b.y), gy = fmaxf(b.z - a.w, a.z - b.w);
+    return !(fmaxf(gx, gy) > size * kBoxSlack);
+}
+
+// The boxes at this lane's step t of `side` leaves from leaf0 on (past those and
+// past the object's last leaf: the last again).
+__device__ __forceinline__ void load_boxes(float4 (&box)[BLOCK_LEAVES], const char *__restrict__ poses, int64_t off,
+                                           int T, int H, int t, int leaf0, int side)
+{
+    const int leaves = (T + LEAF - 1) / LEAF, last = min(leaf0 + side, leaves) - 1;
+    const __amdgpu_buffer_rsrc_t R = pose_rsrc(poses + off, (uint32_t)(leaves * H) * 16u);
+#pragma unroll
+    for (int i = 0; i < BLOCK_LEAVES; ++i)
+        box[i] = load_pose<float4>(R, (uint32_t)min(t, H - 1) * 16u, (uint32_t)(min(leaf0 + i, last) * H) * 16u);
+}
+
+__device__ __forceinline__ float4 join_boxes(const float4 (&b)[BLOCK_LEAVES])
+{
+    static_assert(BLOCK_LEAVES == 4);
+    return box_join(box_join(b[0], b[1]), box_join(b[2], b[3]));
+}
+
+// Which of the blocks (bi, bj0 .. bj0 + n - 1) of a pair have a step to test.
+__device__ __forceinline__ uint32_t blocks_to_test(const DPair &pr, const char *__restrict__ poses, int side, int bi,
+                                                   int bj0, int n)
+{
+    if (pr.box_a < 0) return (1u << n) - 1u;
     const int lane = (int)(threadIdx.x & (WAVE - 1));
-    const int tshift = pr.tshift;
-    const int per = WAVE >> tshift;
-    const int part = lane >> (6 - tshift);
-    const int chunk = (pr.H + (1 << tshift) - 1) >> tshift;
-    const int e = lane & (per - 1);
-    // Item of this lane. Row-major units (bshift = 0) hold the items
-    // item0 .. item0 + E-1; a block unit v is the block (v / nb, v % nb) of
-    // E / 2^bshift rows and 2^bshift columns, which is the same as the
-    // row-major decode of item (first row of the block) * n_jg + first column
-    // + (e / 2^bshift) * n_jg + e % 2^bshift.
-    const int bs = pr.bshift;
-    int f;
-    if (bs == 0) {
-        f = item0 + e;
-    } else {
-        const int v = item0 >> (6 - tshift);
-        const int nb = (n_jg + (1 << bs) - 1) >> bs;
-        const int bi = v / nb;
-        const int c0 = (v - bi * nb) << bs;                // first column of the block
-        const int col = c0 + (e & ((1 << bs) - 1));
-        // a column past the grid's edge is an idle lane
-        f = col < n_jg ? (((bi << (6 - tshift)) >> bs) + (e >> bs)) * n_jg + col : INT_MAX;
+    uint32_t alive = 0;
+    for (int w0 = 0; w0 < pr.H; w0 += WAVE) {
+        const int t = w0 + lane;
+        float4 box[BLOCK_LEAVES];
+        load_boxes(box, poses, pr.box_a, pr.Ta, pr.H, t, bi * side, side);
+        const float4 a = join_boxes(box);
+        const float ma = box_size(a);
+        for (int j = 0; j < n; ++j) {
+            load_boxes(box, poses, pr.box_b, pr.Tb, pr.H, t, (bj0 + j) * side, side);
+            const float4 b = join_boxes(box);
+            if (__any((t < pr.H) & boxes_meet(a, b, fmaxf(ma, box_size(b))))) alive |= 1u << j;
+        }
     }
-    const bool stage = STAGE && bs == 3 && tshift == 0;
-    int ig, jg;
-    bool live = true;  // the lane's item lies in the grid (staged blocks keep every lane to the end)
-    int ig0 = 0, jg0 = 0;
-    if (stage) {
-        const int v = item0 >> 6;
-        const int nb = (n_jg + 7) >> 3;
-        const int bi = v / nb;
-        ig0 = bi << 3;              // the block's first item row and column
-        jg0 = (v - bi * nb) << 3;
-        ig = ig0 + (e >> 3);
-        jg = jg0 + (e & 7);
-        live = ig < n_ig && jg < n_jg;
-    } else {
-        if (f >= n_ig * n_jg) return;  // every part of an item leaves together
-        ig = f / n_jg;
-        jg = f - ig * n_jg;
-    }
-    const int Ta = pr.Ta, Tb = pr.Tb;
-    int ia[RI], jb[RJ];
-#pragma unroll
-    for (int r = 0; r < RI; ++r) ia[r] = min(ig + r * n_ig, Ta - 1);
-#pragma unroll
-    for (int s = 0; s < RJ; ++s) jb[s] = min(jg + s * n_jg, Tb - 1);
-    // Poses are read with buffer loads: the step's offset t * T * sizeof(pose)
-    // lives in a scalar register and the lane offsets are loop-invariant, so
-    // no vector instruction is spent on addressing.
-    const __amdgpu_buffer_rsrc_t A = pose_rsrc(poses + pr.pose_a, (uint32_t)((size_t)pr.H * Ta * sizeof(PA)));
-    const __amdgpu_buffer_rsrc_t B = pose_rsrc(poses + pr.pose_b, (uint32_t)((size_t)pr.H * Tb * sizeof(PB)));
-    const uint32_t strideA = (uint32_t)Ta * (uint32_t)sizeof(PA), strideB = (uint32_t)Tb * (uint32_t)sizeof(PB);
-    // lane offsets: the trajectory and the first step of this lane's part
-    const uint32_t t0 = (uint32_t)min(part * chunk, pr.H - chunk);
-    int first[RI][RJ];
+    return alive;
+}
+
+// A wave's LDS operations complete in order; keeps the compiler from moving
+// its reads above its other lanes' writes, and the other way round.
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// __syncthreads() of the collision kernel. The wait for this wave's own LDS
+// operations is written out: after the loop over the units the compiler (ROCm
+// 7.2) left it out, and the last overlaps of a workgroup were then missed by
+// the waves that were past the barrier before they had landed.
+__device__ __forceinline__ void workgroup_sync()
+{
+    constexpr int kLgkmcnt0 = 0xC07F;   // lgkmcnt(0), the other counters not waited for
+    __builtin_amdgcn_s_waitcnt(kLgkmcnt0);
+    __syncthreads();
+}
+
+constexpr uint32_t kNoHit = ~0u;
+
+// Tests the item (ig, jg) of this lane at `rounds` rounds of S steps, one of
+// each round by this lane's part: of the n steps that lanes 0 .. n-1 hold in
+// `step`, those at k, k - S, ... below the end, from later to earlier. Records
+// each pair's earliest overlap in first[r * stride + s]; returns whether this
+// lane found one. Poses are read with buffer loads, whose range check makes
+// reads past the pose block (positions past the last trajectory) return 0; a
+// position past Ta inside the block is the next step's pose. What such
+// positions find is dropped with the results.
+template <int RI, int RJ, class PA, class PB, class Check>
+__device__ __forceinline__ bool test_item(const DPair &pr, const char *__restrict__ poses, int ig, int jg, int step,
+                                          int k, int rounds, uint32_t *first, int stride, const Check chk)
+{
+    const int S = 1 << pr.tshift;
+    const uint32_t strideA = (uint32_t)pr.Ta * (uint32_t)sizeof(PA), strideB = (uint32_t)pr.Tb * (uint32_t)sizeof(PB);
+    const __amdgpu_buffer_rsrc_t A = pose_rsrc(poses + pr.pose_a, (uint32_t)pr.H * strideA);
+    const __amdgpu_buffer_rsrc_t B = pose_rsrc(poses + pr.pose_b, (uint32_t)pr.H * strideB);
+    const uint32_t oa = (uint32_t)(ig * RI) * (uint32_t)sizeof(PA), ob = (uint32_t)(jg * RJ) * (uint32_t)sizeof(PB);
+    int found[RI][RJ];
 #pragma unroll
     for (int r = 0; r < RI; ++r)
 #pragma unroll
-        for (int s = 0; s < RJ; ++s) first[r][s] = -1;
-
-    if constexpr (STAGE) {
-        if (stage) {
-            // the block's 8 item rows give 8 * RI trajectories of a (entry
-            // r * 8 + row), its 8 columns 8 * RJ of b (entry s * 8 + column)
-            constexpr int NA = 8 * RI, NB = 8 * RJ;
-            __shared__ PA stage_a[WG / WAVE][NA];
-            __shared__ PB stage_b[WG / WAVE][NB];
-            const int w = (int)(threadIdx.x / WAVE);
-            const int ka = lane % NA, kb = lane % NB;
-            const uint32_t la = (uint32_t)min(ig0 + (ka & 7) + (ka >> 3) * n_ig, Ta - 1) * (uint32_t)sizeof(PA);
-            const uint32_t lb = (uint32_t)min(jg0 + (kb & 7) + (kb >> 3) * n_jg, Tb - 1) * (uint32_t)sizeof(PB);
-            const int row = e >> 3, col = e & 7;
-            PA ga = load_pose<PA>(A, la, (uint32_t)(chunk - 1) * strideA);
-            PB gb = load_pose<PB>(B, lb, (uint32_t)(chunk - 1) * strideB);
-            for (int t = chunk - 1; t >= 0; --t) {
-                if (lane < NA) stage_a[w][lane] = ga;
-                if (lane < NB) stage_b[w][lane] = gb;
-                // a wave's LDS operations complete in order; keep the
-                // compiler from moving the reads above the writes
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                if (t > 0) {
-                    ga = load_pose<PA>(A, la, (uint32_t)(t - 1) * strideA);
-                    gb = load_pose<PB>(B, lb, (uint32_t)(t - 1) * strideB);
-                }
-                PA a[RI];
-                PB b[RJ];
+        for (int s = 0; s < RJ; ++s) found[r][s] = -1;
+    for (int m = 0; m < rounds; ++m, k -= S) {
+        const int t = __builtin_amdgcn_ds_bpermute(max(k, 0) << 2, step);
+        const uint32_t va = oa + (uint32_t)t * strideA, vb = ob + (uint32_t)t * strideB;
+        PA a[RI];
+        PB b[RJ];
 #pragma unroll
-                for (int r = 0; r < RI; ++r) a[r] = stage_a[w][r * 8 + row];
+        for (int r = 0; r < RI; ++r) a[r] = load_pose<PA>(A, va + r * (uint32_t)sizeof(PA), 0);
 #pragma unroll
-                for (int s = 0; s < RJ; ++s) b[s] = stage_b[w][s * 8 + col];
+        for (int s = 0; s < RJ; ++s) b[s] = load_pose<PB>(B, vb + s * (uint32_t)sizeof(PB), 0);
 #pragma unroll
-                for (int r = 0; r < RI; ++r)
+        for (int r = 0; r < RI; ++r) a[r] = chk.prep_a(a[r]);
 #pragma unroll
-                    for (int s = 0; s < RJ; ++s)
-                        if (chk(a[r], b[s])) first[r][s] = t;
-                // and the next step's writes below this step's reads
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            }
-            if (!live) return;
-        }
-    }
-    if (!stage) {
-        uint32_t oa[RI], ob[RJ];
-#pragma unroll
-        for (int r = 0; r < RI; ++r) oa[r] = (uint32_t)ia[r] * (uint32_t)sizeof(PA) + t0 * strideA;
-#pragma unroll
-        for (int s = 0; s < RJ; ++s) ob[s] = (uint32_t)jb[s] * (uint32_t)sizeof(PB) + t0 * strideB;
-        for (int t = chunk - 1; t >= 0; --t) {
-            const uint32_t sa = (uint32_t)t * strideA, sb = (uint32_t)t * strideB;
-            PA a[RI];
-            PB b[RJ];
-#pragma unroll
-            for (int r = 0; r < RI; ++r) a[r] = load_pose<PA>(A, oa[r], sa);
-#pragma unroll
-            for (int s = 0; s < RJ; ++s) b[s] = load_pose<PB>(B, ob[s], sb);
-#pragma unroll
-            for (int r = 0; r < RI; ++r)
-#pragma unroll
-                for (int s = 0; s < RJ; ++s)
-                    if (chk(a[r], b[s])) first[r][s] = t;
-        }
-    }
-    if (tshift) {
-        // the earliest hit over the parts: their step ranges cover [0, H), so
-        // it is the smallest step found by any part (lanes l ^ E, l ^ 2E, ...;
-        // the parts of an item are active together)
+        for (int s = 0; s < RJ; ++s) b[s] = chk.prep_b(b[s]);
 #pragma unroll
         for (int r = 0; r < RI; ++r)
 #pragma unroll
-            for (int s = 0; s < RJ; ++s) {
-                const int v = first[r][s] >= 0 ? first[r][s] + (int)t0 : INT_MAX;
-                const int m = min_over_parts(v, tshift);
-                first[r][s] = m == INT_MAX ? -1 : m;
-            }
-        if (part != 0) return;
+            for (int s = 0; s < RJ; ++s)
+                if (chk(a[r], b[s])) found[r][s] = t;
     }
-    // Results: the first hits, and this thread's share of the q sums. A
-    // colliding trajectory pair (i, j) adds p_{b,j} to q_{a,i;b} and p_{a,i}
-    // to q_{b,j;a}; sums are exact integers (p * 2^62), so their value does
-    // not depend on the order in which threads add them.
     bool any = false;
 #pragma unroll
-    for (int r = 0; r < RI; ++r) {
-        const int i = ig + r * n_ig;
+    for (int r = 0; r < RI; ++r)
 #pragma unroll
-        for (int s = 0; s < RJ; ++s) {
-            const int j = jg + s * n_jg;
-            const bool valid = i < Ta && j < Tb;
-            if (!valid) first[r][s] = -1;
-            if (hits && valid) hits[pr.hit_off + (int64_t)i * Tb + j] = (int16_t)first[r][s];
-            any |= first[r][s] >= 0;
-        }
-    }
-    if (any) {
-        unsigned long long pa[RI], pb[RJ];
-#pragma unroll
-        for (int r = 0; r < RI; ++r) pa[r] = pfix[pr.pa_off + ia[r]];
-#pragma unroll
-        for (int s = 0; s < RJ; ++s) pb[s] = pfix[pr.pb_off + jb[s]];
-        if (TL && pr.timeline) {
-            // time-resolved: each colliding pair adds to the sums of its
-            // first colliding slot
-#pragma unroll
-            for (int r = 0; r < RI; ++r)
-#pragma unroll
-                for (int s = 0; s < RJ; ++s)
-                    if (first[r][s] >= 0) {
-                        const int64_t k = first[r][s];
-                        atomicAdd(&hist[pr.ha0 + (k * Ta + (ig + r * n_ig)) * pr.hwa], pb[s]);
-                        atomicAdd(&hist[pr.hb0 + (k * Tb + (jg + s * n_jg)) * pr.hwb], pa[r]);
-                    }
-            return;
-        }
-#pragma unroll
-        for (int r = 0; r < RI; ++r) {
-            unsigned long long row = 0;
-#pragma unroll
-            for (int s = 0; s < RJ; ++s)
-                if (first[r][s] >= 0) row += pb[s];
-            if (row) atomicAdd(&qacc[pr.qa0 + (int64_t)(ig + r * n_ig) * pr.qn], row);
-        }
-#pragma unroll
-        for (int s = 0; s < RJ; ++s) {
-            unsigned long long col = 0;
-#pragma unroll
-            for (int r = 0; r < RI; ++r)
-                if (first[r][s] >= 0) col += pa[r];
-            if (col) atomicAdd(&qacc[pr.qb0 + (int64_t)(jg + s * n_jg) * pr.qn], col);
-        }
-    }
+        for (int s = 0; s < RJ; ++s)
+            if (found[r][s] >= 0) {
+                atomicMin(&first[r * stride + s], (uint32_t)found[r][s]);
+                any = true;
+            }
+    return any;
 }
 
-// EXT: whether this kernel instance carries the extended classes (the
-// point-in-polygon rectangle test and the polygon classes). Their larger
-// code and tiles need more registers, which would lower the occupancy of the
-// plain classes; launches without such pairs use the instance without them.
-// TL: whether it can add to per-slot sums (time-resolved scenes); likewise
-// kept out of the instances that launches without such scenes use.
 // Copies the two polygons of a polygon pair into this wave's LDS slot (each
 // lane a few words), so that their constants reach the tests as vector
 // registers instead of competing for scalar ones.
@@ -939,11 +948,7 @@ __device__ __forceinline__ void stage_polygons(DPoly *slot, const DPoly *__restr
         dst[k] = pa[k];
         dst[words + k] = pb[k];
     }
-    // the wave's LDS operations complete in order; keep the compiler from
-    // moving the reads above the writes
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_lds_fence();
 }
 
 // FAM: the test classes this kernel instance carries. FAM_PLAIN: rectangles
@@ -953,30 +958,27 @@ __device__ __forceinline__ void stage_polygons(DPoly *slot, const DPoly *__restr
 // a launch uses the smallest family that covers its pairs.
 // TL: whether it can add to per-slot sums (time-resolved scenes); likewise
 // kept out of the instances that launches without such scenes use.
-template <int V, int FAM, bool TL, bool STAGE = false>
-__device__ __forceinline__ void collide_work(const DPair &pr, int item0, const char *__restrict__ poses,
-                                             int16_t *__restrict__ hits, const unsigned long long *__restrict__ pfix,
-                                             unsigned long long *__restrict__ qacc,
-                                             unsigned long long *__restrict__ hist, const DPoly *lp)
+template <int V, int FAM>
+__device__ __forceinline__ bool test_items(const DPair &pr, const char *__restrict__ poses, int ig, int jg, int step,
+                                           int k, int rounds, uint32_t *first, int er, int ec, int stride,
+                                           const DPoly *lp)
 {
+#define MHC_TEST(CLS, PA, PB, CHK)                                                                                      \
+    test_item<kTiles[V][CLS].ri, kTiles[V][CLS].rj, PA, PB>(                                                           \
+        pr, poses, ig, jg, step, k, rounds, first + er * kTiles[V][CLS].ri * stride + ec * kTiles[V][CLS].rj, stride, \
+        CHK)
     if constexpr (FAM >= FAM_PIP) {
-        if (pr.cls == CLS_VV_PIP) {
-            collide_items<kTiles[V][CLS_VV_PIP].ri, kTiles[V][CLS_VV_PIP].rj, TL, float4, float4>(
-                pr, item0, poses, hits, pfix, qacc, hist, CheckVVPip{pr.la, pr.wa, pr.lb, pr.wb});
-            return;
-        }
+        if (pr.cls == CLS_VV_PIP) return MHC_TEST(CLS_VV_PIP, float4, float4, CheckVVPip(pr));
     }
     if constexpr (FAM >= FAM_POLY) {
-        const DPoly *P = lp, *Q = lp + 1;  // the pair's polygons (staged)
+        const DPoly *P = lp, *Q = lp + 1;  // the pair's polygons
         switch (pr.cls) {
         case CLS_GG:
         case CLS_GG_PIP: {
             const int shape = (P->k == 8 ? 2 : 0) + (Q->k == 8 ? 1 : 0) + (pr.cls == CLS_GG_PIP ? 4 : 0);
             switch (shape) {
-#define MHC_GG(S, KP, KQ, PIPM)                                                                                      \
-    case S:                                                                                                          \
-        collide_items<1, 1, TL, float4, float4>(pr, item0, poses, hits, pfix, qacc, hist, CheckGG<KP, KQ, PIPM>{P, Q}); \
-        return;
+#define MHC_GG(S, KP, KQ, PIPM) \
+    case S: return MHC_TEST(CLS_GG, float4, float4, (CheckGG<KP, KQ, PIPM>(P, Q)));
                 MHC_GG(0, 4, 4, false)
                 MHC_GG(1, 4, 8, false)
                 MHC_GG(2, 8, 4, false)
@@ -987,109 +989,341 @@ __device__ __forceinline__ void collide_work(const DPair &pr, int item0, const c
                 MHC_GG(7, 8, 8, true)
 #undef MHC_GG
             }
-            return;
+            return false;
         }
         case CLS_GC:
-            if (P->k == 8)
-                collide_items<kTiles[V][CLS_GC].ri, kTiles[V][CLS_GC].rj, TL, float4, float2>(
-                    pr, item0, poses, hits, pfix, qacc, hist, CheckGC<8>{P, pr.rr});
-            else
-                collide_items<kTiles[V][CLS_GC].ri, kTiles[V][CLS_GC].rj, TL, float4, float2>(
-                    pr, item0, poses, hits, pfix, qacc, hist, CheckGC<4>{P, pr.rr});
-            return;
+            return P->k == 8 ? MHC_TEST(CLS_GC, float4, float2, CheckGC<8>(P, pr.rr))
+                             : MHC_TEST(CLS_GC, float4, float2, CheckGC<4>(P, pr.rr));
         case CLS_CG:
-            if (P->k == 8)
-                collide_items<kTiles[V][CLS_CG].ri, kTiles[V][CLS_CG].rj, TL, float2, float4>(
-                    pr, item0, poses, hits, pfix, qacc, hist, CheckCG<8>{P, pr.rr});
-            else
-                collide_items<kTiles[V][CLS_CG].ri, kTiles[V][CLS_CG].rj, TL, float2, float4>(
-                    pr, item0, poses, hits, pfix, qacc, hist, CheckCG<4>{P, pr.rr});
-            return;
+            return P->k == 8 ? MHC_TEST(CLS_CG, float2, float4, CheckCG<8>(P, pr.rr))
+                             : MHC_TEST(CLS_CG, float2, float4, CheckCG<4>(P, pr.rr));
         default:
             break;
         }
     }
     switch (pr.cls) {
-    case CLS_VV:
-        collide_items<kTiles[V][CLS_VV].ri, kTiles[V][CLS_VV].rj, TL, float4, float4, CheckVV, STAGE>(
-            pr, item0, poses, hits, pfix, qacc, hist, CheckVV{pr.la, pr.wa, pr.lb, pr.wb});
-        break;
-    case CLS_VP:
-        collide_items<kTiles[V][CLS_VP].ri, kTiles[V][CLS_VP].rj, TL, float4, float2, CheckVP, STAGE>(
-            pr, item0, poses, hits, pfix, qacc, hist, CheckVP{pr.la, pr.wa, pr.rr});
-        break;
-    case CLS_PV:
-        collide_items<kTiles[V][CLS_PV].ri, kTiles[V][CLS_PV].rj, TL, float2, float4, CheckPV, STAGE>(
-            pr, item0, poses, hits, pfix, qacc, hist, CheckPV{pr.lb, pr.wb, pr.rr});
-        break;
-    default:
-        collide_items<kTiles[V][CLS_PP].ri, kTiles[V][CLS_PP].rj, TL, float2, float2, CheckPP, STAGE>(
-            pr, item0, poses, hits, pfix, qacc, hist, CheckPP{pr.rr});
-        break;
+    case CLS_VV: return MHC_TEST(CLS_VV, float4, float4, CheckVV(pr));
+    case CLS_VP: return MHC_TEST(CLS_VP, float4, float2, CheckVP(pr));
+    case CLS_PV: return MHC_TEST(CLS_PV, float2, float4, CheckPV(pr));
+    default: return MHC_TEST(CLS_PP, float2, float2, CheckPP(pr));
+    }
+#undef MHC_TEST
+}
+
+// The pair that strip g of the launch belongs to: the last p with strip0[p] <= g,
+// by the wave's 64 lanes together (two rounds for up to 4096 pairs).
+__device__ __forceinline__ int pair_of_strip(const int64_t *__restrict__ strip0, int n_pairs, int64_t g)
+{
+    const int lane = (int)(threadIdx.x & (WAVE - 1));
+    int lo = 0, len = n_pairs;
+    while (len > 1) {
+        const int step = (len + WAVE - 1) / WAVE;
+        const int k = lane * step;
+        const bool le = k < len && strip0[lo + min(k, len - 1)] <= g;
+        const int last = (__popcll(__ballot(le)) - 1) * step;
+        lo += last;
+        len = min(step, len - last);
+    }
+    return __builtin_amdgcn_readfirstlane(lo);
+}
+
+// Waves per SIMD that an instance is held to: three workgroups a CU for the
+// rectangle and circle classes (80 vector registers; two, with 94, measured
+// 412 against 357 us on the 40-object stress scene and 28 against 23 us on the
+// 3-object road with the point-in-polygon test), two for the polygon classes.
+template <int FAM>
+constexpr int kCollideMinWaves = FAM == FAM_POLY ? 4 : 6;
+
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// What the results of a block need of its pair.
+struct BlockLds {
+    int Ta, Tb, wa, wb, na;  // trajectory counts, lanes of the per-slot sums (0: none), objects
+    int pad;
+    int64_t hit, qa, qb;     // first-hit entry and q sums of (i = 0, j = 0)
+    int64_t ha, hb;          // per-slot sums of slot 0, i = 0 and j = 0
+};
+
+// The LDS of a collision workgroup: the blocks of the round that have steps to
+// test, and of the K2_SLOTS of them that are taken together
+struct K2Lds {
+    int4 alive[K2_SLOTS * MAX_STRIP];               // pair, block row, block column, horizon
+    BlockLds block[K2_SLOTS];
+    uint32_t first[K2_SLOTS * BLOCK_PAIRS];         // earliest overlap of every trajectory pair, [slot][row][column]
+    unsigned long long mask[K2_UNITS];              // steps to test of the units that have any
+    uint32_t unit[K2_UNITS];                        // slot, window, time split and unit of the block (unit_word)
+    unsigned long long leaf_mask[K2_SLOTS][BLOCK_LEAVES * BLOCK_LEAVES];
+    // trajectories at the blocks' rows and columns, their integer
+    // probabilities, and the sums over the colliding pairs of a row or column
+    int ti[K2_SLOTS][BLOCK_SIDE], tj[K2_SLOTS][BLOCK_SIDE];
+    unsigned long long pa[K2_SLOTS][BLOCK_SIDE], pb[K2_SLOTS][BLOCK_SIDE];
+    unsigned long long sum_a[K2_SLOTS][BLOCK_SIDE], sum_b[K2_SLOTS][BLOCK_SIDE];
+    int n_alive[3], n_units[3], any_hit;
+};
+
+__device__ __forceinline__ uint32_t unit_word(int slot, int window, int tshift, int u)
+{
+    return (uint32_t)(slot << 16 | window << 15 | tshift << 12 | u);
+}
+
+// Lists the units of the block in a slot that have steps to test among w0 ..
+// w0 + 127, by one wave: lane l looks at step l of a window of 64, for all the
+// block's pairs of leaves; a unit's steps are those of its leaves.
+__device__ __forceinline__ void list_units(K2Lds &w, int *n_units, int slot, const DPair &pr, int side, int bi, int bj,
+                                           int w0, const char *__restrict__ poses)
+{
+    const int lane = (int)(threadIdx.x & (WAVE - 1)), H = pr.H;
+    const int na = (pr.Ta + LEAF - 1) / LEAF - bi * side, nb = (pr.Tb + LEAF - 1) / LEAF - bj * side;
+    // lane u: unit u of the block
+    const int ur = lane >> pr.block_ucs, uc = lane & ((1 << pr.block_ucs) - 1);
+    const bool unit = ur < pr.block_ur && bi * pr.block_ur + ur < pr.nui && (bj << pr.block_ucs) + uc < pr.nuj;
+    for (int window = 0; window < 2 && w0 + window * WAVE < H; ++window) {
+        const int t = w0 + window * WAVE + lane;
+        unsigned long long mine = 0;   // lane i * 4 + j: of leaf i of a and j of b
+        if (pr.box_a < 0) {
+            mine = __ballot(t < H);
+        } else {
+            float4 a[BLOCK_LEAVES], b[BLOCK_LEAVES];
+            load_boxes(a, poses, pr.box_a, pr.Ta, H, t, bi * side, side);
+            load_boxes(b, poses, pr.box_b, pr.Tb, H, t, bj * side, side);
+            float mb[BLOCK_LEAVES];
+#pragma unroll
+            for (int j = 0; j < BLOCK_LEAVES; ++j) mb[j] = box_size(b[j]);
+#pragma unroll
+            for (int i = 0; i < BLOCK_LEAVES; ++i) {
+                if (i >= side) break;
+                const float ma = box_size(a[i]);
+#pragma unroll
+                for (int j = 0; j < BLOCK_LEAVES; ++j) {
+                    if (j >= side) break;
+                    const unsigned long long m = __ballot((t < H) & boxes_meet(a[i], b[j], fmaxf(ma, mb[j])));
+                    if (lane == i * BLOCK_LEAVES + j) mine = m;
+                }
+            }
+        }
+        if (lane < BLOCK_LEAVES * BLOCK_LEAVES)
+            w.leaf_mask[slot][lane] = lane / BLOCK_LEAVES < min(na, side) && lane % BLOCK_LEAVES < min(nb, side) ? mine : 0ull;
+        wave_lds_fence();
+        if (unit) {
+            const int i0 = ur << pr.unit_rs, j0 = uc << pr.unit_cs;
+            const int i1 = (i0 + (1 << pr.unit_rs) - 1) / LEAF, j1 = (j0 + (1 << pr.unit_cs) - 1) / LEAF;
+            unsigned long long m = 0;
+            for (int i = i0 / LEAF; i <= i1; ++i)
+                for (int j = j0 / LEAF; j <= j1; ++j) m |= w.leaf_mask[slot][i * BLOCK_LEAVES + j];
+            if (m) {
+                const int at = atomicAdd(n_units, 1);
+                w.mask[at] = m;
+                w.unit[at] = unit_word(slot, window, pr.tshift, lane);
+            }
+        }
+        wave_lds_fence();   // before the next window's leaf masks
     }
 }
 
-// Collision kernel: every wave owns one slot of the host-built plan and runs
-// its segments. For plans of contiguous stretches (large scenes) the slots
-// are numbered XCD-major (workgroups are dealt to the XCDs in turn), so the
-// pairs one XCD works on stay together in its L2; for individually packed
-// plans neighbouring slots are spread over the XCDs and CUs, which mixes the
-// load-heavy and arithmetic-heavy test classes on every CU. The host
-// balances the slots by the exact instruction cost of the work, so every
-// SIMD finishes together without any cross-XCD atomics.
-// The plain-class instances are held to at least 5 waves per SIMD and the
-// point-in-polygon ones to 4: with fewer the vector ALU idles on pose loads,
-// and without the bound the compiler's occupancy heuristic may trade a wave
-// for registers it does not need.
-template <int FAM>
-constexpr int kCollideMinWaves = FAM == FAM_PLAIN ? 5 : FAM == FAM_PIP ? 4 : 1;
-
-// A launch may run one part of the plan (part of n_parts): every wave then
-// takes only its units [U part / n_parts, U (part + 1) / n_parts) of the U
-// units of its segments, so that n_parts launches cover each unit once.
-template <int V, int FAM, bool TL, bool STAGE>
-__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(kCollideMinWaves<FAM>))) void k2_collide(const DPair *__restrict__ pairs, const WorkItem *__restrict__ work,
-                                                 const int32_t *__restrict__ bins, int n_bins, int xcd_major,
-                                                 const char *__restrict__ poses, int16_t *__restrict__ hits,
-                                                 const unsigned long long *__restrict__ pfix,
-                                                 unsigned long long *__restrict__ qacc,
-                                                 unsigned long long *__restrict__ hist, const DPoly *__restrict__ polys,
-                                                 int part, int n_parts)
+// Fills in the results part of a slot, by one wave.
+__device__ __forceinline__ void block_tables(K2Lds &w, int slot, const DPair &pr, int side_leaves, int bi, int bj,
+                                             const DObj *__restrict__ objs, const unsigned long long *__restrict__ pfix)
 {
-    const int wave_in_block = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
-    const int blocks = (int)gridDim.x;
-    const int xcd = (int)blockIdx.x % N_XCD, round = (int)blockIdx.x / N_XCD;
-    const int per_xcd = (blocks / N_XCD) * (WG / WAVE);
-    int slot;
-    if (xcd_major && (int)blockIdx.x < (blocks / N_XCD) * N_XCD)
-        slot = xcd * per_xcd + round * (WG / WAVE) + wave_in_block;
-    else
-        slot = (int)blockIdx.x * (WG / WAVE) + wave_in_block;  // grid not a multiple of the XCD count
-    if (slot >= n_bins) return;
+    const int lane = (int)(threadIdx.x & (WAVE - 1)), x = lane & (BLOCK_SIDE - 1);
+    const int side = side_leaves * LEAF;
+    const DObj &oa = objs[pr.a], &ob = objs[pr.b];
+    // the first half of the wave a's rows, the second b's columns
+    const bool is_row = lane < BLOCK_SIDE;
+    const int pos = (is_row ? bi : bj) * side + x, T = is_row ? oa.T : ob.T;
+    const int i = x < side && pos < T ? (is_row ? traj_at(pos, oa.n_u, oa.n_w, oa.strip)
+                                                : traj_at(pos, ob.n_u, ob.n_w, ob.strip)) : -1;
+    const unsigned long long p = i >= 0 ? pfix[(is_row ? oa.traj_off : ob.traj_off) + i] : 0ull;
+    (is_row ? w.ti : w.tj)[slot][x] = i;
+    (is_row ? w.pa : w.pb)[slot][x] = p;
+    (is_row ? w.sum_a : w.sum_b)[slot][x] = 0ull;
+    if (lane == 0) {
+        BlockLds &b = w.block[slot];
+        b.Ta = oa.T;
+        b.Tb = ob.T;
+        b.na = oa.n_scene_obj;
+        b.wa = oa.timeline ? oa.tl_w : 0;
+        b.wb = ob.tl_w;
+        b.hit = pr.hit_off;
+        b.qa = oa.q_row + ob.local;
+        b.qb = ob.q_row + oa.local;
+        b.ha = oa.hist_off + ob.local;
+        b.hb = ob.hist_off + oa.local;
+    }
+}
+
+// Collision kernel. The launch's blocks (up to 32 x 32 trajectory pairs) are
+// looked at in strips of a block row, pair after pair, in rounds: in round r
+// wave w of workgroup b takes a strip of row r * 8 + w (grid strips a row,
+// strip_in_row) and finds out from the two groups' boxes in which of its
+// blocks any step can hold an overlap. The few such blocks are then taken by
+// the workgroup together, eight at a time, for every 128 steps of the horizon:
+//   - a wave per block finds the steps to test of the block's units from the
+//     boxes of their leaves, and lists the units that have any, while another
+//     looks up what the results will need;
+//   - the listed units' rounds of S steps are dealt evenly to the waves, which
+//     test them and keep the earliest overlap of every pair in LDS;
+// and last the pairs that overlap are stored and summed up. Which blocks meet
+// is known to nobody beforehand, so work is spread in three ways: a workgroup's
+// strips of a round come from far apart in the sequence, the strips of a pair
+// are in an order that keeps neighbours apart (strip_at), and inside a
+// workgroup no wave owns a unit. With most blocks gone after one look, a
+// launch is bound by the latency of its dependent reads (pair, boxes, poses,
+// tables: 1 to 2 us each when first touched on a CU), so each of them is made
+// once per block, by waves side by side.
+// A launch may run one part of the plan: rounds [round0, round1). The plan's
+// strips fill full_rows rows and last_row strips of the next.
+template <int V, int FAM, bool TL>
+__global__ __launch_bounds__(K2_WG) __attribute__((amdgpu_waves_per_eu(kCollideMinWaves<FAM>))) void k2_collide(
+    const DPair *__restrict__ pairs, const DObj *__restrict__ objs, const int64_t *__restrict__ strip0, int n_pairs,
+    int full_rows, int last_row, int strip_len, int side_shift, int round0, int round1, const char *__restrict__ poses,
+    int16_t *__restrict__ hits, const unsigned long long *__restrict__ pfix, unsigned long long *__restrict__ qacc,
+    unsigned long long *__restrict__ hist, const DPoly *__restrict__ polys)
+{
+    constexpr int NW = K2_WG / WAVE;
+    const int side = (1 << side_shift) / LEAF;   // leaves to a side of a block
+    // Rounds of S steps that a wave tests at a time: few where the waves of a
+    // workgroup hardly fill (octagons 34 us with 2, 38 with 4), more where
+    // there is work for all of them and an item's set-up counts (stress scene
+    // 332 us with 4, 357 with 2; 64-scene batch 470 and 510).
+    const int item_rounds = strip_len > 1 ? 4 : 2;
+    static_assert(NW == K2_SLOTS);
+    const int tid = (int)threadIdx.x, lane = tid & (WAVE - 1), wave = uniform(tid / WAVE);
     // per wave: the two polygons of its current polygon pair
     constexpr bool poly = FAM >= FAM_POLY;
-    __shared__ DPoly lds_polys[poly ? 2 * (WG / WAVE) : 1];
-    DPoly *lp = lds_polys + (poly ? 2 * wave_in_block : 0);
-    const int s0 = bins[slot], s1 = bins[slot + 1];
-    int lo = 0, hi = INT_MAX;   // this launch's units of the wave
-    if (n_parts > 1) {
-        int units = 0;
-        for (int k = s0; k < s1; ++k) units += work[k].n_units;
-        lo = (int)((int64_t)units * part / n_parts);
-        hi = (int)((int64_t)units * (part + 1) / n_parts);
+    __shared__ DPoly lds_polys[poly ? 2 * NW : 1];
+    __shared__ K2Lds w;
+    DPoly *lp = lds_polys + (poly ? 2 * wave : 0);
+    // The counters n_alive and n_units go round three places: one is used now,
+    // the next one is emptied before a barrier. That one was last read before
+    // the barrier of the use before this one, which every wave has passed.
+    if (tid < 3) w.n_alive[tid] = w.n_units[tid] = 0;
+    if (tid == 0) w.any_hit = 0;
+    workgroup_sync();
+    auto next = [](int at) { return at == 2 ? 0 : at + 1; };
+    int alive_at = 0, units_at = 0;
+    for (int r = round0; r < round1; ++r) {
+        const int row = r * NW + wave, x = strip_in_row(row, (int)blockIdx.x, (int)gridDim.x);
+        if (row < full_rows || (row == full_rows && x < last_row)) {
+            const int64_t g = (int64_t)row * gridDim.x + x;
+            const int p = pair_of_strip(strip0, n_pairs, g);
+            const DPair &pr = pairs[p];
+            int bi, bj;
+            strip_at(pr, (uint32_t)(g - strip0[p]), &bi, &bj);
+            bj *= strip_len;
+            const uint32_t alive = blocks_to_test(pr, poses, side, bi, bj, min(strip_len, pr.nbj - bj));
+            if (lane < strip_len && alive >> lane & 1u)
+                w.alive[atomicAdd(&w.n_alive[alive_at], 1)] = make_int4(p, bi, bj + lane, pr.H);
+        }
+        if (tid == 0) w.n_alive[next(alive_at)] = 0;
+        workgroup_sync();
+        const int n = uniform(w.n_alive[alive_at]);
+        alive_at = next(alive_at);
+        for (int k0 = 0; k0 < n; k0 += K2_SLOTS) {
+            const int slots = min(n - k0, K2_SLOTS);
+            int H = 0;
+            for (int k = 0; k < slots; ++k) H = max(H, uniform(w.alive[k0 + k].w));
+            // up to four blocks: the tables by the other waves
+            const int tables = 2 * slots <= NW ? NW - 1 - wave : wave;
+            for (int q = tid; q < slots << 2 * side_shift; q += K2_WG) w.first[q] = kNoHit;
+            for (int w0 = 0; w0 < H; w0 += 2 * WAVE) {
+                if (wave < slots) {
+                    const int4 b = w.alive[k0 + wave];
+                    list_units(w, &w.n_units[units_at], wave, pairs[uniform(b.x)], side, uniform(b.y), uniform(b.z), w0,
+                               poses);
+                }
+                if (w0 == 0 && tables < slots) {
+                    const int4 b = w.alive[k0 + tables];
+                    block_tables(w, tables, pairs[uniform(b.x)], side, uniform(b.y), uniform(b.z), objs, pfix);
+                }
+                if (tid == 0) w.n_units[next(units_at)] = 0;
+                workgroup_sync();
+                // the tests
+                const int n_units = uniform(w.n_units[units_at]);
+                units_at = next(units_at);
+                int turn = 0;   // items of the units before
+                for (int x0 = 0; x0 < n_units; x0 += WAVE) {
+                    // lane l: unit x0 + l, its items (item_rounds rounds of
+                    // S steps) and those of the units before it
+                    const int x = min(x0 + lane, n_units - 1);
+                    const int ts = w.unit[x] >> 12 & 7;
+                    const int rounds = (__popcll(w.mask[x]) + (1 << ts) - 1) >> ts;
+                    const int upto = scan_add_int(x0 + lane < n_units ? (rounds + item_rounds - 1) / item_rounds : 0);
+                    const int items = __builtin_amdgcn_readlane(upto, WAVE - 1);
+                    for (int it = (wave - turn) & (NW - 1); it < items; it += NW) {
+                        const int l = __popcll(__ballot(upto <= it));
+                        const int m0 = (it - (l ? __builtin_amdgcn_readlane(upto, l - 1) : 0)) * item_rounds;
+                        const unsigned long long mask = w.mask[x0 + l];
+                        const int word = uniform((int)w.unit[x0 + l]), slot = word >> 16, u = word & 0xFFF;
+                        const int4 b = w.alive[k0 + slot];
+                        const DPair &pr = pairs[uniform(b.x)];
+                        if (poly && pr.cls >= CLS_GG) stage_polygons(lp, polys, pr);
+                        const int ur = u >> pr.block_ucs, uc = u & ((1 << pr.block_ucs) - 1);
+                        const int per = WAVE >> pr.tshift, e = lane & (per - 1), part = lane >> (6 - pr.tshift);
+                        const int er = e >> pr.bshift, ec = e & ((1 << pr.bshift) - 1);
+                        // lane i < n_steps gets the i-th step to test
+                        const int n_steps = __popcll(mask);
+                        const int rank = (int)__builtin_amdgcn_mbcnt_hi(
+                            (uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+                        const int dest = (mask >> lane) & 1ull ? rank : n_steps + lane - rank;
+                        const int step = __builtin_amdgcn_ds_permute(dest << 2, w0 + (word >> 15 & 1) * WAVE + lane);
+                        const bool any = test_items<V, FAM>(
+                            pr, poses, (uniform(b.y) * pr.block_ur + ur) * (per >> pr.bshift) + er,
+                            (((uniform(b.z) << pr.block_ucs) + uc) << pr.bshift) + ec, step,
+                            n_steps - 1 - (m0 << pr.tshift) - part,
+                            min(((n_steps + (1 << pr.tshift) - 1) >> pr.tshift) - m0, item_rounds),
+                            &w.first[(((slot << side_shift) + (ur << pr.unit_rs)) << side_shift) + (uc << pr.unit_cs)], er,
+                            ec, 1 << side_shift, lp);
+                        if (any) w.any_hit = 1;
+                    }
+                    turn += items;
+                }
+                workgroup_sync();
+            }
+            // Results: the first hits of colliding trajectory pairs (the
+            // entries start at -1), and the blocks' share of the q sums. A
+            // colliding pair (i, j) adds p_{b,j} to q_{a,i;b} and p_{a,i} to
+            // q_{b,j;a}; sums are exact integers (p * 2^62), so their value
+            // does not depend on the order of the adds.
+            if (!uniform(w.any_hit)) continue;
+            for (int q = tid; q < slots << 2 * side_shift; q += K2_WG) {
+                const uint32_t f = w.first[q];
+                if (f == kNoHit) continue;
+                const int k = q >> 2 * side_shift;
+                const int rr = (q >> side_shift) & ((1 << side_shift) - 1), cc = q & ((1 << side_shift) - 1);
+                const int i = w.ti[k][rr], j = w.tj[k][cc];
+                if (i < 0 || j < 0) continue;
+                const BlockLds &b = w.block[k];
+                if (hits) hits[b.hit + (int64_t)i * b.Tb + j] = (int16_t)f;
+                if (TL && b.wa) {
+                    // time-resolved: each colliding pair adds to the sums of
+                    // its first colliding slot
+                    atomicAdd(&hist[b.ha + ((int64_t)f * b.Ta + i) * b.wa], w.pb[k][cc]);
+                    atomicAdd(&hist[b.hb + ((int64_t)f * b.Tb + j) * b.wb], w.pa[k][rr]);
+                } else {
+                    atomicAdd(&w.sum_a[k][rr], w.pb[k][cc]);
+                    atomicAdd(&w.sum_b[k][cc], w.pa[k][rr]);
+                }
+            }
+            workgroup_sync();
+            if (tid == 0) w.any_hit = 0;
+            if (wave < slots) {
+                const BlockLds &b = w.block[wave];
+                const int x = lane & (BLOCK_SIDE - 1);
+                const bool is_row = lane < BLOCK_SIDE;
+                const unsigned long long sum = (is_row ? w.sum_a : w.sum_b)[wave][x];
+                if (sum) atomicAdd(&qacc[is_row ? b.qa + (int64_t)w.ti[wave][x] * b.na : b.qb + (int64_t)w.tj[wave][x] * b.na], sum);
+            }
+            workgroup_sync();   // before the next blocks' tables
+        }
+        if (n > 0) workgroup_sync();   // before the next round's blocks
     }
-    int base = 0;   // units of the wave's segments before segment k
-    for (int k = s0; k < s1 && base < hi; ++k) {
-        const WorkItem w = work[k];
-        const int u0 = max(lo - base, 0), u1 = min(hi - base, w.n_units);
-        base += w.n_units;
-        if (u0 >= u1) continue;
-        const DPair pr = pairs[w.pair];
-        if (poly && pr.cls >= CLS_GG) stage_polygons(lp, polys, pr);
-        const int per = WAVE >> pr.tshift;
-        for (int u = u0; u < u1; ++u)
-            collide_work<V, FAM, TL, STAGE>(pr, w.item0 + u * per, poses, hits, pfix, qacc, hist, lp);
-    }
+}
+
+// -1 over the first hits, for a collision stage that runs without the
+// trajectory stage of the same call (which writes them otherwise).
+__global__ __launch_bounds__(WG) void k2_clear(int16_t *__restrict__ hits, int64_t n_hits)
+{
+    clear_hits(hits, n_hits, (int64_t)blockIdx.x, (int64_t)gridDim.x);
 }
 
 // ===========================================================================
@@ -1500,68 +1734,78 @@ hipError_t launch_trajgen(const Launch &L, hipStream_t s)
 {
     if (L.n_obj <= 0) return hipSuccess;
     if (L.one_track)
-        hipLaunchKernelGGL(k1_trajgen<true>, dim3(L.k1_x, L.k1_nrows), dim3(WG), 0, s, L.objs, L.vals, L.poses, L.p,
-                           L.pfix, L.qacc, L.done, L.hist, L.k1_rows);
+        hipLaunchKernelGGL(k1_trajgen<true>, dim3(L.k1_x, L.k1_nrows), dim3(K1_WG), 0, s, L.objs, L.vals, L.poses, L.p,
+                           L.pfix, L.qacc, L.done, L.hist, L.k1_rows, L.hits, L.n_hits);
     else
-        hipLaunchKernelGGL(k1_trajgen<false>, dim3(L.k1_x, L.k1_nrows), dim3(WG), 0, s, L.objs, L.vals, L.poses, L.p,
-                           L.pfix, L.qacc, L.done, L.hist, L.k1_rows);
+        hipLaunchKernelGGL(k1_trajgen<false>, dim3(L.k1_x, L.k1_nrows), dim3(K1_WG), 0, s, L.objs, L.vals, L.poses, L.p,
+                           L.pfix, L.qacc, L.done, L.hist, L.k1_rows, L.hits, L.n_hits);
     return hipGetLastError();
 }
 
-template <int V, int FAM, bool TL, bool STAGE>
+static hipError_t launch_clear_hits(const Launch &L, hipStream_t s)
+{
+    if (!L.hits || L.n_hits <= 0) return hipSuccess;
+    // 16 KB a workgroup, at most 8 workgroups a CU
+    const int64_t blocks = std::min<int64_t>((L.n_hits * 2 + (16 << 10) - 1) / (16 << 10), 2048);
+    hipLaunchKernelGGL(k2_clear, dim3((unsigned)blocks), dim3(WG), 0, s, L.hits, L.n_hits);
+    return hipGetLastError();
+}
+
+template <int V, int FAM, bool TL>
 static hipError_t launch_k2(const Launch &L, hipStream_t s)
 {
-    const int blocks = (L.n_bins + WG / WAVE - 1) / (WG / WAVE);
     const int parts = L.collide_parts > 1 ? L.collide_parts : 1;
     const int first = L.collide_only > 0 ? L.collide_only - 1 : 0;
     const int last = L.collide_only > 0 ? L.collide_only : parts;
     if (first >= parts) return hipErrorInvalidValue;
+    const int64_t per_round = (int64_t)L.k2_grid * (K2_WG / WAVE);
+    const int64_t rounds = (L.n_strips + per_round - 1) / per_round;
+    if (rounds * (K2_WG / WAVE) >= INT_MAX) return hipErrorInvalidValue;
     for (int part = first; part < last; ++part) {
-        hipLaunchKernelGGL((k2_collide<V, FAM, TL, STAGE>), dim3(blocks), dim3(WG), 0, s, L.pairs, L.work, L.bins,
-                           L.n_bins, L.xcd_major, L.poses, L.hits, L.pfix, L.qacc, L.hist, L.polys, part, parts);
+        hipLaunchKernelGGL((k2_collide<V, FAM, TL>), dim3(L.k2_grid), dim3(K2_WG), 0, s, L.pairs, L.objs, L.strip0, L.n_pairs,
+                           (int)(L.n_strips / L.k2_grid), (int)(L.n_strips % L.k2_grid), L.strip_len, L.side_shift,
+                           (int)(rounds * part / parts), (int)(rounds * (part + 1) / parts), L.poses, L.hits, L.pfix,
+                           L.qacc, L.hist, L.polys);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
 }
 
-template <int V, int FAM, bool TL, bool STAGE>
+template <int V, int FAM, bool TL>
 static int k2_resident_blocks()
 {
     int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k2_collide<V, FAM, TL, STAGE>, WG, 0) != hipSuccess ||
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k2_collide<V, FAM, TL>, K2_WG, 0) != hipSuccess ||
         per_cu < 1)
         per_cu = 1;
     return per_cu;
 }
 
-// The kernel instance of (variant, class family, per-slot sums, LDS-staged
-// blocks): F::run<V, FAM, TL, STAGE>() is called for the instance. Staged
-// instances exist for the plain family without per-slot sums only.
-template <int FAM, bool TL, bool STAGE, class F>
+// The kernel instance of (variant, class family, per-slot sums):
+// F::run<V, FAM, TL>() is called for the instance.
+template <int FAM, bool TL, class F>
 static auto with_variant(int variant, const F &f)
 {
     switch (variant) {
-    case 0: return f.template run<0, FAM, TL, STAGE>();
-    case 1: return f.template run<1, FAM, TL, STAGE>();
-    case 2: return f.template run<2, FAM, TL, STAGE>();
-    default: return f.template run<3, FAM, TL, STAGE>();
+    case 0: return f.template run<0, FAM, TL>();
+    case 1: return f.template run<1, FAM, TL>();
+    case 2: return f.template run<2, FAM, TL>();
+    default: return f.template run<3, FAM, TL>();
     }
 }
 
 template <int FAM, class F>
 static auto with_timeline(int variant, bool tl, const F &f)
 {
-    return tl ? with_variant<FAM, true, false>(variant, f) : with_variant<FAM, false, false>(variant, f);
+    return tl ? with_variant<FAM, true>(variant, f) : with_variant<FAM, false>(variant, f);
 }
 
 template <class F>
-static auto with_instance(int variant, int family, bool tl, bool stage, const F &f)
+static auto with_instance(int variant, int family, bool tl, const F &f)
 {
     switch (family) {
-    case FAM_PLAIN:
-        if (stage && !tl) return with_variant<FAM_PLAIN, false, true>(variant, f);
-        return with_timeline<FAM_PLAIN>(variant, tl, f);
+    case FAM_PLAIN: return with_timeline<FAM_PLAIN>(variant, tl, f);
     case FAM_PIP: return with_timeline<FAM_PIP>(variant, tl, f);
     default: return with_timeline<FAM_POLY>(variant, tl, f);
     }
@@ -1570,26 +1814,31 @@ static auto with_instance(int variant, int family, bool tl, bool stage, const F 
 struct LaunchK2 {
     const Launch &L;
     hipStream_t s;
-    template <int V, int FAM, bool TL, bool STAGE>
-    hipError_t run() const { return launch_k2<V, FAM, TL, STAGE>(L, s); }
+    template <int V, int FAM, bool TL>
+    hipError_t run() const { return launch_k2<V, FAM, TL>(L, s); }
 };
 
 struct ResidentK2 {
-    template <int V, int FAM, bool TL, bool STAGE>
-    int run() const { return k2_resident_blocks<V, FAM, TL, STAGE>(); }
+    template <int V, int FAM, bool TL>
+    int run() const { return k2_resident_blocks<V, FAM, TL>(); }
 };
 
 hipError_t launch_collide(const Launch &L, hipStream_t s)
 {
-    if (L.n_work <= 0) return hipSuccess;
-    if (L.variant < 0 || L.variant >= N_VARIANTS || L.family < FAM_PLAIN || L.family > FAM_POLY)
+    if (L.n_strips <= 0) return hipSuccess;
+    if (L.variant < 0 || L.variant >= N_VARIANTS || L.family < FAM_PLAIN || L.family > FAM_POLY || L.k2_grid < 1 ||
+        L.strip_len < 1 || L.strip_len > MAX_STRIP)
         return hipErrorInvalidValue;
-    return with_instance(L.variant, L.family, L.timeline != 0, L.stage != 0, LaunchK2{L, s});
+    if (L.clear_hits) {
+        const hipError_t e = launch_clear_hits(L, s);
+        if (e != hipSuccess) return e;
+    }
+    return with_instance(L.variant, L.family, L.timeline != 0, LaunchK2{L, s});
 }
 
-int collide_blocks_per_cu(int variant, int family, bool timeline, bool stage)
+int collide_blocks_per_cu(int variant, int family, bool timeline, bool waves)
 {
-    return with_instance(variant, family, timeline, stage, ResidentK2{});
+    return with_instance(variant, family, timeline, ResidentK2{}) * (waves ? K2_WG / WAVE : 1);
 }
 
 // ===========================================================================

@@ -49,80 +49,104 @@ enum RiskModel : int32_t { RISK_EXCLUSIVE = 0, RISK_INDEPENDENT = 1 };
 // One object of one scene. Offsets are global across all scenes of a launch.
 struct DObj {
     int32_t kind, n_u, n_w, T;
-    int32_t has_score, H;
+    int32_t strip, H;             // traj_at's strip height
     int32_t local, n_scene_obj;   // index within its scene, object count of the scene
     int32_t risk, timeline;       // RiskModel of its scene; 1: time-resolved risk
     int32_t tl_w;                 // time-resolved: lanes per trajectory, the power of two >= n_scene_obj
     int32_t model;                // motion model (mhc.h MHC_MODEL_*)
     int64_t traj_off;             // index of trajectory 0 in the p / traj_crit arrays
     int64_t q_row;                // q index of (this object, i = 0, b = 0)
-    int64_t pose_off;             // byte offset of the pose block [H][T]
-    int64_t frame_off;            // vehicles: byte offset of the block [H][T] of the same poses in
-                                  // their own frame, (K_x, K_y, cos, sin) with K = c in that frame
-    int64_t u_off, w_off, score_off;  // offsets (doubles) into the value array
+    int64_t pose_off;             // byte offset of the pose block [H][T], by position (traj_at)
+    int64_t box_off;              // byte offset of the leaves' boxes [leaf][H] (x_min, x_max, y_min, y_max);
+                                  // -1: none (the collision kernel tests every step)
+    int64_t u_off, w_off, score_off;  // offsets (doubles) into the value array; score_off -1: uniform
     int64_t obj_out;              // index in the object_crit array
     // time-resolved risk (timeline scenes only)
     int64_t hist_off;             // slot sums [s][i][b < tl_w]: index of (s = 0, i = 0, b = 0)
     int64_t tl_traj;              // [s][i] criticality over time, and traj_crit_t (i, s): index of i = 0, s = 0
     int64_t tl_obj;               // crit_t index of (this object, s = 0)
     int64_t tl_att;               // attrib index of (this object, b = 0)
+    float hl, hw;                 // half length and half width the shape's bounds are taken from, rounded up
     double x, y, heading, speed;  // position relative to the scene origin (scene_origin)
     double tau;
     double params[6];             // motion-model parameters
 };
 
 // One object pair (a < b within its scene). The collision kernel covers the
-// T_a x T_b trajectory pairs as a flat list of n_ig * n_jg "items": item f is
-// the micro-tile ig = f / n_jg, jg = f % n_jg, holding trajectories
-// i = ig + r*n_ig (r < RI) and j = jg + s*n_jg (s < RJ).
+// T_a x T_b trajectory pairs as a grid of n_ig x n_jg "items": item (ig, jg) is
+// the micro-tile of the positions ig*RI + r (r < RI) of a and jg*RJ + s
+// (s < RJ) of b.
 struct DPair {
     int32_t a, b;                 // global object indices
     int32_t cls, H;
     int32_t Ta, Tb;
     int32_t n_ig, n_jg;
     int64_t hit_off;              // first-hit entry of (i = 0, j = 0)
-    int64_t pose_a, pose_b;       // byte offsets of the two pose blocks (a rectangle whose tests take
-                                  // its pose in its own frame: the object's frame block)
+    int64_t pose_a, pose_b;       // byte offsets of the two pose blocks
+    int64_t box_a, box_b;         // byte offsets of the two objects' leaf boxes, -1: none
     float la, wa, lb, wb;         // half length / half width of vehicles
     float rr;                     // squared test radius: r_Q^2 (rect-circle), (r_P + r_Q)^2 (circle-circle)
-    int32_t qn;                   // q row stride: object count of the scene
-    int32_t tshift;               // time split S = 2^tshift (S <= H): a unit's steps run in S parts
-    int64_t qa0;                  // q index of (a, i = 0, b)
-    int64_t qb0;                  // q index of (b, j = 0, a)
-    int64_t pa_off, pb_off;       // trajectory index of (a, 0) and (b, 0)
-    int32_t timeline;             // 1: q sums go to the per-slot sums below
-    int32_t hwa, hwb;             // lanes per trajectory of a's and of b's per-slot sums
+    int32_t tshift;               // time split S = 2^tshift (S <= H): a unit's steps go round S parts of the wave
+    int32_t nui, nuj;             // grid of the pair's units
+    int32_t unit_rs, unit_cs;     // log2 of a unit's positions of a and of b
+    int32_t block_ur, block_ucs;  // units of a block: block_ur rows by 2^block_ucs columns
+    int32_t nbi, nbj;             // grid of its blocks
+    int32_t nsj;                  // strips of a block row
+    int32_t step_i, step_j;       // strip_at's order of them
     int32_t poly_a, poly_b;       // DPoly of a and of b (polygon classes), else -1
-    int32_t bshift;               // unit shape: 0 = E consecutive items of the row-major item grid;
-                                  // else blocks of (E >> bshift) item rows x 2^bshift item columns
-    int64_t ha0;                  // slot-sum index of (a: s = 0, i = 0, b); slot s, trajectory i at + (s*Ta + i)*hwa
-    int64_t hb0;                  // slot-sum index of (b: s = 0, j = 0, a); + (s*Tb + j)*hwb
+    int32_t bshift;               // unit shape: (E >> bshift) item rows x 2^bshift item columns, E = 64 >> tshift
 };
 
-// A run of collision work for one wave: n_units consecutive units of a pair.
-// A pair's items (ig, jg) form an n_ig x n_jg grid; with time split S a unit
-// holds E = 64 / S of them, and lane l takes item l % E of unit item0 / E + u
-// and the c = ceil(H/S) steps from min(p*c, H - c) of part p = l / E, so the
-// S parts of an item run side by side in one wave and cover every step (the
-// last part overlaps its neighbour where S does not divide H). With bshift = 0 the items of unit v are
-// E*v .. E*v + E-1 in row-major order; otherwise unit v is the block
-// (v / nb, v % nb) of the grid cut into blocks of E / 2^bshift rows and
-// 2^bshift columns (nb blocks per block row), so that a wave reads few
-// distinct poses of either object per step. Items past the grid are idle
-// lanes. The host assigns every wave of the collision kernel a range of
-// segments.
-struct WorkItem {
-    int32_t pair;
-    int32_t item0;
-    int32_t n_units;
-    int32_t pad;
-};
+// A pair's items (ig, jg) form an n_ig x n_jg grid, cut into nui x nuj units of
+// E / 2^bshift item rows and 2^bshift item columns, E = 64 / S with time split
+// S. In a unit lane l takes item l % E and every S-th of the steps the unit has
+// to test, those of part l / E, so S steps of an item run side by side in one
+// wave. Items past the grid are idle lanes. Units are looked at a block at a
+// time (block_ur x 2^block_ucs units, a square of positions), blocks in
+// strips of a block row: strip of the pair's sequence number u, each strip
+// once. Consecutive strips are step_i block rows (coprime to nbi) and step_j
+// strips apart.
+__host__ __device__ inline void strip_at(const DPair &pr, uint32_t u, int *bi, int *sj)
+{
+    const uint32_t q = u / (uint32_t)pr.nbi, ru = u - q * (uint32_t)pr.nbi;
+    *bi = (int)(ru * (uint32_t)pr.step_i % (uint32_t)pr.nbi);
+    *sj = (int)((q + ru * (uint32_t)pr.step_j) % (uint32_t)pr.nsj);
+}
 
-constexpr int WG = 256;           // threads per workgroup, all kernels
+// The strip of its row of `grid` strips that workgroup x looks at: the
+// workgroups are turned from row to row, so that none meets the same part of
+// every pair.
+__host__ __device__ inline int strip_in_row(int row, int x, int grid)
+{
+    const uint32_t c = ((uint32_t)(row & 0xFFFF) * 40503u) % (uint32_t)grid + (uint32_t)x;
+    return (int)(c < (uint32_t)grid ? c : c - (uint32_t)grid);
+}
+
+// The trajectory (index k * n_w + l of the n_u x n_w control grid) at a
+// position of its object. Positions run through strips of `strip` rows of the
+// grid (accelerations or speeds), column by column, the next strip backwards:
+// neighbouring positions are neighbours in both controls, so a leaf of them,
+// and a group of leaves, keeps close together over the horizon.
+__host__ __device__ inline int traj_at(int pos, int n_u, int n_w, int strip)
+{
+    const int b = pos / (strip * n_w);
+    const int k0 = b * strip, left = n_u - k0, rows = left < strip ? left : strip;
+    const int r = pos - k0 * n_w;
+    const int c = r / rows;
+    return (k0 + (r - c * rows)) * n_w + ((b & 1) ? n_w - 1 - c : c);
+}
+
+constexpr int WG = 256;           // threads per workgroup, other kernels
 constexpr int WAVE = 64;          // wavefront size
 constexpr int MAX_TSHIFT = 3;     // time split of a collision unit: S <= 8
-constexpr int N_XCD = 8;          // accelerator complex dies; workgroups are dealt to them in turn
-constexpr int K1_TPB = WG / 64;   // trajectories per trajectory workgroup (one wave each)
+constexpr int K1_WG = 512;         // threads per workgroup of the trajectory kernel
+constexpr int K2_WG = 512;         // and of the collision kernel
+constexpr int K1_TPB = K1_WG / 64; // trajectories per trajectory workgroup (one wave each)
+constexpr int LEAF = K1_TPB;      // trajectories of consecutive positions that share a box per step
+// A pose with a coordinate beyond kBoxMax (or not finite) makes its leaf's box
+// infinite; a step is left out of the tests where the boxes lie apart by more
+// than kBoxSlack times their largest coordinate.
+constexpr float kBoxMax = 1e15f, kBoxSlack = 0x1p-16f;
 // q sums are accumulated exactly as integers. EXCLUSIVE reading: p scaled by
 // 2^62 and rounded (sum <= 1). INDEPENDENT reading: -log(1 - p), capped at 64,
 // scaled by 2^56 and rounded; over one object's trajectories (sum p = 1) the
@@ -133,25 +157,33 @@ constexpr double kLScale = 72057594037927936.0;          // 2^56
 constexpr double kLInvScale = 1.3877787807814457e-17;    // 2^-56
 constexpr double kLCap = 64.0;                           // exp(-64) rounds 1 - q to 0
 
+// A collision block holds at most BLOCK_LEAVES leaves, BLOCK_SIDE positions, of
+// either object; a strip at most MAX_STRIP blocks of a block row. A collision
+// workgroup takes K2_SLOTS blocks together, up to K2_UNITS listed units (a unit
+// holds at least MIN_UNIT_PAIRS pairs, for two windows of 64 steps).
+constexpr int BLOCK_LEAVES = 4, BLOCK_SIDE = BLOCK_LEAVES * LEAF, BLOCK_PAIRS = BLOCK_SIDE * BLOCK_SIDE;
+constexpr int MAX_STRIP = 8, MIN_UNIT_PAIRS = 32, K2_SLOTS = K2_WG / WAVE;
+constexpr int K2_UNITS = 2 * K2_SLOTS * BLOCK_PAIRS / MIN_UNIT_PAIRS;
+
 // Micro-tile shape per class, selected by a kernel variant id.
 struct TileShape {
     int ri, rj;
 };
 constexpr int N_VARIANTS = 4;
 // variant -> shape per class {VV, VP, PV, PP, VV_PIP, GG, GG_PIP, GC, CG}.
-// The shapes keep the VALU cost of one work unit similar across classes (25,
-// 12, 6 and 58 VALU per rect-rect, rect-circle, circle-circle and
-// point-in-polygon test; 100-500 for polygon pairs) and the loads per test
-// low: a rectangle-circle tile pairs each rectangle pose (read in its own
-// frame) with 4 or 8 circles. Variants 2 and 3 cut the work into more,
-// smaller units for scenes with few of them.
+// The shapes keep the loads per test low (25, 12, 6 and 58 VALU per rect-rect,
+// rect-circle, circle-circle and point-in-polygon test, 100-500 for polygon
+// pairs): a rectangle-circle tile pairs each rectangle pose (taken to its own
+// frame) with 2 or 4 circles, and with a time split of 8 the tiles of variants 0
+// and 1 make units of one pair of leaves. Variants 2 and 3 cut the work into
+// smaller units.
 // Polygon-polygon pairs always take one test per thread (their tests are
 // long, and the kernel has one code path per padded vertex-count pair).
 constexpr TileShape kTiles[N_VARIANTS][N_CLS] = {
-    {{4, 2}, {2, 4}, {4, 2}, {4, 4}, {4, 2}, {1, 1}, {1, 1}, {4, 1}, {1, 4}},
-    {{4, 2}, {2, 8}, {8, 2}, {4, 4}, {4, 2}, {1, 1}, {1, 1}, {4, 1}, {1, 4}},
-    {{2, 2}, {2, 4}, {4, 2}, {4, 4}, {2, 1}, {1, 1}, {1, 1}, {2, 2}, {2, 2}},
-    {{2, 1}, {1, 4}, {4, 1}, {4, 2}, {1, 1}, {1, 1}, {1, 1}, {1, 1}, {1, 1}},
+    {{4, 2}, {2, 4}, {4, 2}, {4, 2}, {4, 2}, {1, 1}, {1, 1}, {4, 1}, {1, 4}},
+    {{2, 4}, {4, 2}, {2, 4}, {2, 4}, {2, 4}, {1, 1}, {1, 1}, {2, 2}, {2, 2}},
+    {{2, 2}, {2, 2}, {2, 2}, {2, 2}, {2, 2}, {1, 1}, {1, 1}, {4, 1}, {1, 4}},
+    {{4, 1}, {1, 4}, {4, 1}, {2, 2}, {4, 1}, {1, 1}, {1, 1}, {1, 1}, {1, 1}},
 };
 static_assert(kTiles[0][CLS_GG].ri == 1 && kTiles[1][CLS_GG].ri == 1 && kTiles[2][CLS_GG].ri == 1 &&
                   kTiles[3][CLS_GG].ri == 1 && kTiles[0][CLS_GG].rj == 1 && kTiles[1][CLS_GG].rj == 1 &&
@@ -161,24 +193,36 @@ static_assert(kTiles[0][CLS_GG_PIP].ri == 1 && kTiles[1][CLS_GG_PIP].ri == 1 && 
                   kTiles[3][CLS_GG_PIP].ri == 1 && kTiles[0][CLS_GG_PIP].rj == 1 && kTiles[1][CLS_GG_PIP].rj == 1 &&
                   kTiles[2][CLS_GG_PIP].rj == 1 && kTiles[3][CLS_GG_PIP].rj == 1,
               "polygon-polygon tiles are 1 x 1");
+constexpr bool tiles_fit()
+{
+    for (const auto &v : kTiles)
+        for (const TileShape &t : v)
+            if ((t.ri & (t.ri - 1)) || (t.rj & (t.rj - 1)) || t.ri > 8 || t.rj > 8)
+                return false;
+    return true;
+}
+static_assert(tiles_fit(), "tile sides are powers of two, at most 8");
 
 // Launch entry points (kernels.hip).
 struct Launch {
     const DObj *objs;
     const double *vals;
     const DPair *pairs;
-    const WorkItem *work;
     char *poses;
     unsigned long long *pfix;     // p * 2^62, per trajectory
     unsigned long long *qacc;     // integer q sums [n_q]
-    const int32_t *bins;          // [n_bins+1] segment range of each collision wave slot
+    const int64_t *strip0;        // [n_pairs+1] first strip of collision blocks of each pair
     const DPoly *polys;           // polygons of the polygon pairs
     double *p;
     int16_t *hits;
     double *q;
     double *traj_crit;
     double *obj_crit;
-    int n_obj, n_pairs, n_work, n_bins;
+    int n_obj, n_pairs;
+    int64_t n_strips, n_hits;     // strips of collision blocks, first-hit entries
+    int strip_len;                // blocks of a strip
+    int side_shift;               // log2 of the positions to a side of a block
+    int k2_grid;                  // workgroups of the collision kernel
     int k1_x;                     // trajectory kernel grid x: blocks of a row
     int k1_nrows;                 // trajectory kernel grid y: rows (objects, or k1_rows entries)
     const int2 *k1_rows;          // per row: object and its first block; null when row = object
@@ -192,15 +236,16 @@ struct Launch {
     double *att_w;                // attribution [b][i] per object
     double *ct_w;                 // criticality over time [s][i] per object
     double *crit_t, *traj_crit_t, *attrib, *traj_attrib;
-    int xcd_major;                // plan of contiguous stretches: number the slots XCD-major
     int collide_parts;            // the collision plan runs as this many launches (0 or 1: one)
     int collide_only;             // 0: launch every part; k > 0: launch only part k - 1
+    int clear_hits;               // collide writes -1 over the first hits first (no trajgen in this call does)
     int one_track;                // some object follows the one-track model (heavier trajectory kernel)
-    int stage;                    // collision instance that stages 8 x 8 item blocks in LDS
     int variant;
     int family;                   // ClassFamily covering every pair of the launch
 };
 
+// trajgen also writes -1 (no collision) over the first hits, of which collide
+// stores the colliding pairs' only
 hipError_t launch_trajgen(const Launch &L, hipStream_t s);
 hipError_t launch_collide(const Launch &L, hipStream_t s);
 // risk: the time-resolved kernels (timeline launches) and the risk kernel
@@ -212,8 +257,8 @@ constexpr int kMaxDevices = 64;
 // This GPU's address of that array (the device must be current on the
 // calling thread); looked up once per device, then cached.
 hipError_t noalloc_scratch_address(int device, char **out);
-// resident workgroups per CU of the collision kernel for a variant, class
-// family, with or without the per-slot sums, with or without LDS-staged blocks
-int collide_blocks_per_cu(int variant, int family, bool timeline, bool stage);
+// resident workgroups (or their waves) per CU of the collision kernel for a
+// variant, class family, with or without the per-slot sums
+int collide_blocks_per_cu(int variant, int family, bool timeline, bool waves);
 
 }  // namespace mhc

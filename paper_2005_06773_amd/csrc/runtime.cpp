@@ -47,73 +47,84 @@ int scene_family(const mhc_scene *s)
     return s->overlap == MHC_OVERLAP_PIP ? FAM_PIP : FAM_PLAIN;
 }
 
-// Relative VALU cost of one check per class, for longest-first ordering; the
-// polygon classes scale with the vertex counts (class_cost).
-static const double kClsCost[N_CLS] = {25.0, 12.0, 12.0, 6.4, 60.0, 0.0, 0.0, 0.0, 0.0};
-
-double class_cost(int cls, int k_a, int k_b)
-{
-    switch (cls) {
-    case CLS_GG:
-    case CLS_GG_PIP: return 14.0 + 4.0 * (k_a + k_b) + 6.0 * k_a * k_b;
-    case CLS_GC: return 8.0 + 13.0 * k_a;
-    case CLS_CG: return 8.0 + 13.0 * k_b;
-    default: return kClsCost[cls];
-    }
-}
-
 // Padded vertex count of an object's polygon in a polygon pair (4 for a
 // rectangle, 4 or 8 for an outline).
 static int padded_vertices(int n) { return n <= 4 ? 4 : MAX_VERTICES; }
-static int poly_vertices(const mhc_object &o) { return padded_vertices(o.n_vertices > 0 ? o.n_vertices : 4); }
-// Per-unit cost outside the step loop (setup, result stores), same units.
-static const double kUnitOverhead = 120.0;
-// From this many work units per collision wave on, waves take contiguous
-// stretches of the unit sequence instead of individually packed units.
-static const int kContiguousUnitsPerWave = 8;
-// Below this many work units per resident collision wave, units are split in
-// time (up to S = 8 parts side by side in a wave) to get more, shorter
-// units. Around one unit per wave the split costs more than it balances
-// (measured on the 11-object scene: 40.5 us with S = 2 against 37.0 us).
-static const double kSplitBelowUnitsPerWave = 0.75;
+// Below this many collision units per resident wave, units are split in time
+// (up to S = 8 steps of an item side by side in a wave): units of 8 x 8 pairs,
+// one pair of leaves, whose boxes separate more steps than those of the 32 x 16
+// pairs of an unsplit unit. Split or not (collision kernel): 383 or 467 us on
+// the 64-scene batch (85 unsplit units a wave), 319 or 329 us on the stress
+// scene (260). A GPU partition of few waves was not measured and keeps the
+// split to plans of few units.
+static double split_below_units_per_wave(int max_waves) { return max_waves < 1024 ? 16.0 : 1000.0; }
 
-// Collision units of a pair with time split 2^tshift (E = 64 >> tshift items
-// per unit): E consecutive items of the row-major item grid (bshift = 0), or
-// blocks of E >> bshift item rows by 2^bshift item columns.
-static int64_t pair_units(const DPair &pr, int tshift, int bshift)
+// How many blocks a plan should have per resident wave: the largest side of a
+// block (8, 16 or 32 positions) that still gives as many is taken. Larger
+// blocks take fewer looks, smaller ones spread the pairs that meet over more
+// workgroups. Collision kernel on the 11-object scene: 13 us with half a block
+// a wave (sides of 32), 17 with one (16: a second round of looks); octagons,
+// whose tests take 30 times as long, 34 us with two blocks a wave, 47 with half
+// a block.
+static double blocks_per_wave(int family) { return family == FAM_POLY ? 2.0 : 0.5; }
+
+// The strip height of traj_at for an n_u x n_w grid: a leaf's positions cover
+// about as large a share of either control's range.
+static int strip_height(int n_u, int n_w)
 {
-    const int64_t per = WAVE >> tshift;
-    if (bshift == 0) return ((int64_t)pr.n_ig * pr.n_jg + per - 1) / per;
-    const int64_t rows = per >> bshift, cols = (int64_t)1 << bshift;
-    return ((pr.n_ig + rows - 1) / rows) * ((pr.n_jg + cols - 1) / cols);
+    const int h = (int)std::lround(std::sqrt((double)LEAF * n_u / n_w));
+    return std::min(std::max(h, 1), n_u);
 }
 
-// Unit shape of a pair. A row-major unit reads, at every step, the poses of
-// one or two a-items and of E b-items; a block of 8 x 8 items reads 8 of each,
-// about a third of the cache lines, which matters once the scene's poses no
-// longer fit in an XCD's L2. Blocks are taken where they add at most 1/32 of
-// idle lanes (grids whose sides are near multiples of the block's).
-static int unit_shape(const DPair &pr, int tshift)
+// Collision units of a pair with time split 2^tshift (E = 64 >> tshift items a
+// unit) in blocks of E >> bs item rows by 2^bs item columns.
+static int64_t pair_units(const DPair &pr, int tshift, int bs, int *nui = nullptr, int *nuj = nullptr)
 {
-    const int64_t lin = pair_units(pr, tshift, 0);
-    int best = 0;
-    int64_t best_u = 0;
-    for (int bs = 3; bs <= 4; ++bs) {  // 8 or 16 item columns
-        if (((WAVE >> tshift) >> bs) < 1) break;
-        const int64_t u = pair_units(pr, tshift, bs);
-        if (u * 32 <= lin * 33 && (best == 0 || u < best_u)) {
+    const int rows = (WAVE >> tshift) >> bs, cols = 1 << bs;
+    const int bi = (pr.n_ig + rows - 1) / rows, bj = (pr.n_jg + cols - 1) / cols;
+    if (nui) *nui = bi;
+    if (nuj) *nuj = bj;
+    return (int64_t)bi * bj;
+}
+
+// Unit shape of a pair: bs of the block whose positions (ri and rj to an item
+// row and column) have the smallest perimeter, so that few leaves meet it,
+// among those that need at most a quarter more units than the fewest.
+static int unit_shape(const DPair &pr, int tshift, const TileShape &ts)
+{
+    int64_t fewest = INT64_MAX;
+    const int top = 6 - tshift;
+    auto fits = [&](int bs) {
+        return ((WAVE >> tshift) >> bs) * ts.ri <= BLOCK_SIDE && (1 << bs) * ts.rj <= BLOCK_SIDE;
+    };
+    for (int bs = 0; bs <= top; ++bs)
+        if (fits(bs)) fewest = std::min(fewest, pair_units(pr, tshift, bs));
+    int best = -1, best_side = 0;
+    for (int bs = 0; bs <= top; ++bs) {
+        if (!fits(bs) || pair_units(pr, tshift, bs) * 4 > fewest * 5) continue;
+        const int side = ((WAVE >> tshift) >> bs) * ts.ri + (1 << bs) * ts.rj;
+        if (best < 0 || side < best_side) {
             best = bs;
-            best_u = u;
+            best_side = side;
         }
     }
     return best;
 }
 
+// A step through n block rows (or columns) that is coprime to n, about 0.38 n.
+static int coprime_step(int n)
+{
+    if (n <= 1) return 0;
+    int s = std::max(1, (int)std::lround(0.382 * n));
+    while (std::gcd(s, n) != 1) ++s;
+    return s % n;
+}
+
 // Steps per part of a unit with time split 2^tshift: ceil(H / S).
 static int split_chunk(int H, int tshift) { return (H + (1 << tshift) - 1) >> tshift; }
 
-// A split fits a horizon when every part has a step and the parts' overlap
-// (S * ceil(H / S) - H steps tested twice) is at most an eighth of H.
+// A split fits a horizon when every part has a step and a walk through all
+// steps leaves at most an eighth of H idle (S * ceil(H / S) - H).
 static bool split_fits(int H, int tshift)
 {
     const int S = 1 << tshift;
@@ -273,8 +284,7 @@ static void reset_layout(Layout &L)
     keep(fresh.objs, L.objs);
     keep(fresh.vals, L.vals);
     keep(fresh.pairs, L.pairs);
-    keep(fresh.work, L.work);
-    keep(fresh.bins, L.bins);
+    keep(fresh.strip0, L.strip0);
     keep(fresh.polys, L.polys);
     keep(fresh.sc, L.sc);
     keep(fresh.k1_rows, L.k1_rows);
@@ -282,33 +292,23 @@ static void reset_layout(Layout &L)
 }
 
 static void build_layout_once(const mhc_scene *scenes, int n_scenes, int variant, int max_waves, Layout &L,
-                              bool with_hits, int max_tshift);
+                              bool with_hits, bool boxes);
 
 void build_layout(const mhc_scene *scenes, int n_scenes, int variant, int max_waves, Layout &L, bool with_hits,
-                  int max_waves_staged, int max_tshift)
+                  size_t max_bytes)
 {
-    max_tshift = std::min(std::max(max_tshift, 0), MAX_TSHIFT);
-    build_layout_once(scenes, n_scenes, variant, max_waves, L, with_hits, max_tshift);
-    const bool stage = L.family == FAM_PLAIN && !L.timeline && max_waves > 0 && L.staged_share >= 0.5;
-    if (stage && max_waves_staged > 0 && max_waves_staged != max_waves)
-        build_layout_once(scenes, n_scenes, variant, max_waves_staged, L, with_hits, max_tshift);
-    L.stage = stage;
+    build_layout_once(scenes, n_scenes, variant, max_waves, L, with_hits, true);
+    if (L.total_bytes > max_bytes) build_layout_once(scenes, n_scenes, variant, max_waves, L, with_hits, false);
 }
 
 static void build_layout_once(const mhc_scene *scenes, int n_scenes, int variant, int max_waves, Layout &L,
-                              bool with_hits, int max_tshift)
+                              bool with_hits, bool boxes)
 {
     reset_layout(L);
     L.variant = variant;
     L.with_hits = with_hits;
-    struct PairCost {
-        double c;        // cost of one of the pair's work units
-        int32_t pidx;
-        int32_t n_units;
-    };
-    std::vector<PairCost> costs;
+    L.boxes = boxes;
     std::vector<std::pair<int, int>> plist;
-    std::vector<int> pair_vertices;   // per pair: polygon vertex counts of a and b
     for (int k = 0; k < n_scenes; ++k) {
         const mhc_scene &s = scenes[k];
         const int n = s.n_objects;
@@ -333,7 +333,6 @@ static void build_layout_once(const mhc_scene *scenes, int n_scenes, int variant
             d.n_u = o.n_u;
             d.n_w = o.n_w;
             d.T = o.n_u * o.n_w;
-            d.has_score = o.score != nullptr;
             d.H = s.horizon;
             d.local = a;
             d.n_scene_obj = n;
@@ -360,14 +359,15 @@ static void build_layout_once(const mhc_scene *scenes, int n_scenes, int variant
             d.q_row = L.n_q + toff * n;
             d.pose_off = (int64_t)L.pose_bytes;
             L.pose_bytes += align256((size_t)s.horizon * d.T * (o.kind == MHC_VEHICLE ? 16 : 8));
-            d.frame_off = -1;
-            if (o.kind == MHC_VEHICLE) {
-                d.frame_off = (int64_t)L.pose_bytes;
-                L.pose_bytes += align256((size_t)s.horizon * d.T * 16);
+            d.strip = strip_height(o.n_u, o.n_w);
+            d.box_off = -1;
+            if (boxes) {
+                d.box_off = (int64_t)L.pose_bytes;
+                L.pose_bytes += align256((size_t)s.horizon * ((d.T + LEAF - 1) / LEAF) * sizeof(float4));
             }
             d.u_off = (int64_t)L.vals.size();
             d.w_off = d.u_off + o.n_u;
-            d.score_off = d.w_off + o.n_w;
+            d.score_off = o.score ? d.w_off + o.n_w : -1;
             L.vals.resize(L.vals.size() + o.n_u + o.n_w + (o.score ? d.T : 0));
             d.obj_out = L.n_obj + a;
             L.k3_x = std::max(L.k3_x, (d.T + WG - 1) / WG);
@@ -394,8 +394,6 @@ static void build_layout_once(const mhc_scene *scenes, int n_scenes, int variant
             pr.cls = pair_class(oa.kind, ob.kind, s.overlap, oa.n_vertices > 0, ob.n_vertices > 0);
             pr.poly_a = poly_of[a];
             pr.poly_b = poly_of[b];
-            pair_vertices.push_back(poly_vertices(oa));
-            pair_vertices.push_back(poly_vertices(ob));
             L.family = std::max(L.family, class_family(pr.cls));
             pr.H = s.horizon;
             pr.Ta = oa.n_u * oa.n_w;
@@ -404,24 +402,11 @@ static void build_layout_once(const mhc_scene *scenes, int n_scenes, int variant
             pr.n_ig = (pr.Ta + ts.ri - 1) / ts.ri;
             pr.n_jg = (pr.Tb + ts.rj - 1) / ts.rj;
             pr.hit_off = L.n_hits + hoff;
-            // the rectangle-rectangle tests take b's pose in b's frame, the
-            // rectangle-circle tests the rectangle's (frame blocks)
-            const bool frame_a = pr.cls == CLS_VP;
-            const bool frame_b = pr.cls == CLS_VV || pr.cls == CLS_VV_PIP || pr.cls == CLS_PV;
-            pr.pose_a = frame_a ? L.objs[obj_base + a].frame_off : L.objs[obj_base + a].pose_off;
-            pr.pose_b = frame_b ? L.objs[obj_base + b].frame_off : L.objs[obj_base + b].pose_off;
-            pr.qn = n;
-            pr.qa0 = L.objs[obj_base + a].q_row + b;
-            pr.qb0 = L.objs[obj_base + b].q_row + a;
-            pr.pa_off = L.objs[obj_base + a].traj_off;
-            pr.pb_off = L.objs[obj_base + b].traj_off;
-            pr.timeline = s.timeline;
-            if (s.timeline) {
-                pr.hwa = L.objs[obj_base + a].tl_w;
-                pr.hwb = L.objs[obj_base + b].tl_w;
-                pr.ha0 = L.objs[obj_base + a].hist_off + b;
-                pr.hb0 = L.objs[obj_base + b].hist_off + a;
-            }
+            const DObj &da = L.objs[obj_base + a], &db = L.objs[obj_base + b];
+            pr.pose_a = da.pose_off;
+            pr.pose_b = db.pose_off;
+            pr.box_a = da.box_off;
+            pr.box_b = db.box_off;
             L.pairs.push_back(pr);
             hoff += (int64_t)pr.Ta * pr.Tb;
             ext.checks += (int64_t)pr.Ta * pr.Tb * s.horizon;
@@ -470,132 +455,68 @@ static void build_layout_once(const mhc_scene *scenes, int n_scenes, int variant
             L.k1_nrows = (int)(L.k1_rows.size() / 2);
         }
     }
-    // Time split. With few units for the resident waves, a unit's steps are
-    // cut into S parts that run side by side in one wave (64/S items,
-    // ceil(H/S) steps per lane): S times as many, S times shorter units, which
-    // the packing below can spread evenly and which fill the GPU. S is the
-    // smallest of 1, 2, 4, 8 that gives enough units (the largest allowed for
-    // the size bound, max_waves = 0), lowered per pair until it fits the
-    // horizon (split_fits).
-    int want = max_tshift;
+    // Time split. With few units for the resident waves, S steps of an item
+    // run side by side in a wave (64/S items per unit). S is the smallest of
+    // 1, 2, 4, 8 that gives enough units (the largest for the size bound,
+    // max_waves = 0), lowered per pair until it fits the horizon (split_fits).
+    int want = MAX_TSHIFT;
     if (max_waves > 0) {
-        for (want = 0; want < max_tshift; ++want) {
+        for (want = 0; want < MAX_TSHIFT; ++want) {
             int64_t u = 0;
-            for (const DPair &pr : L.pairs) u += pair_units(pr, want, 0);
-            if ((double)u >= kSplitBelowUnitsPerWave * max_waves) break;
+            for (const DPair &pr : L.pairs) {
+                const TileShape ts = kTiles[variant][pr.cls];
+                u += pair_units(pr, want, unit_shape(pr, want, ts));
+            }
+            if ((double)u >= split_below_units_per_wave(max_waves) * max_waves) break;
         }
     }
-    for (size_t pidx = 0; pidx < L.pairs.size(); ++pidx) {
-        DPair &pr = L.pairs[pidx];
+    L.n_units = 0;
+    for (DPair &pr : L.pairs) {
         int sh = want;
-        while (sh > 0 && !split_fits(pr.H, sh)) --sh;
-        pr.tshift = sh;
-        pr.bshift = unit_shape(pr, sh);
         const TileShape ts = kTiles[variant][pr.cls];
-        const int ka = pr.poly_a >= 0 ? pair_vertices[2 * pidx] : 0, kb = pr.poly_b >= 0 ? pair_vertices[2 * pidx + 1] : 0;
-        // a wave executes every step of every test of a unit, whether or
-        // not all of its lanes hold an item
-        // (rectangle-rectangle and rectangle-circle tests: 25 and 12 VALU each,
-        // the rectangle's frame read ready from its frame block)
-        const double per_test = class_cost(pr.cls, ka, kb);
-        const double unit_cost = (double)ts.ri * ts.rj * split_chunk(pr.H, sh) * per_test + kUnitOverhead;
-        costs.push_back(PairCost{unit_cost, (int32_t)pidx, (int32_t)pair_units(pr, sh, pr.bshift)});
+        while (sh > 0 && (!split_fits(pr.H, sh) || (WAVE >> sh) * ts.ri * ts.rj < MIN_UNIT_PAIRS)) --sh;
+        pr.tshift = sh;
+        pr.bshift = unit_shape(pr, sh, kTiles[variant][pr.cls]);
+        L.n_units += pair_units(pr, sh, pr.bshift, &pr.nui, &pr.nuj);
     }
-
-    // Collision plan: every wave slot gets a list of segments of work units.
-    int64_t n_units = 0;
-    double total_cost = 0.0, staged_cost = 0.0;
-    for (const PairCost &pc : costs) {
-        n_units += pc.n_units;
-        total_cost += pc.c * pc.n_units;
-        const DPair &pr = L.pairs[pc.pidx];
-        if (pr.bshift == 3 && pr.tshift == 0) staged_cost += pc.c * pc.n_units;
-    }
-    L.staged_share = total_cost > 0.0 ? staged_cost / total_cost : 0.0;
-    const int n_bins = (int)std::max<int64_t>(1, std::min<int64_t>(n_units, max_waves > 0 ? max_waves : n_units));
-    L.work.clear();
-    L.bins.assign(n_bins + 1, 0);
-    L.contiguous = n_units >= (int64_t)kContiguousUnitsPerWave * n_bins;
-    if (L.contiguous) {
-        // Many units per wave: each slot takes the next stretch of the unit
-        // sequence (pairs in scene order) worth total/n_bins of cost, so the
-        // plan is O(pairs + waves) and neighbouring slots, which sit on one
-        // XCD, work on neighbouring pairs.
-        const double per_slot = total_cost / n_bins;
-        size_t p = 0;
-        int32_t u = 0;
-        double acc = 0.0;
-        for (int sl = 0; sl < n_bins; ++sl) {
-            L.bins[sl] = (int32_t)L.work.size();
-            const double goal = (sl + 1) * per_slot;
-            while (p < costs.size()) {
-                const PairCost &pc = costs[p];
-                const int32_t left = pc.n_units - u;
-                int32_t k = left;
-                if (sl < n_bins - 1) {
-                    const double want = std::floor((goal - acc) / pc.c + 0.5);
-                    k = (int32_t)std::max(0.0, std::min((double)left, want));
-                }
-                if (k > 0) {
-                    L.work.push_back(WorkItem{pc.pidx, u * (WAVE >> L.pairs[pc.pidx].tshift), k, 0});
-                    acc += pc.c * k;
-                    u += k;
-                }
-                if (u == pc.n_units) {
-                    ++p;
-                    u = 0;
-                } else {
-                    break;
-                }
-            }
+    // Collision plan: the pairs' strips of blocks one after another, looked at
+    // in rounds by as many waves as the GPU holds (k2_collide).
+    int64_t n_blocks = 0;
+    auto unit_rows = [&](const DPair &pr) { return ((WAVE >> pr.tshift) >> pr.bshift) * kTiles[variant][pr.cls].ri; };
+    auto unit_cols = [&](const DPair &pr) { return (1 << pr.bshift) * kTiles[variant][pr.cls].rj; };
+    int least = LEAF;   // no unit is larger than a block
+    for (const DPair &pr : L.pairs) least = std::max({least, unit_rows(pr), unit_cols(pr)});
+    for (int side = BLOCK_SIDE; side >= least; side /= 2) {
+        n_blocks = 0;
+        L.side_shift = 0;
+        while ((1 << L.side_shift) < side) ++L.side_shift;
+        for (DPair &pr : L.pairs) {
+            const int rows = unit_rows(pr), cols = unit_cols(pr);
+            for (pr.unit_rs = 0; (1 << pr.unit_rs) < rows;) ++pr.unit_rs;
+            for (pr.unit_cs = 0; (1 << pr.unit_cs) < cols;) ++pr.unit_cs;
+            pr.block_ur = side / rows;
+            pr.block_ucs = L.side_shift - pr.unit_cs;
+            pr.nbi = (pr.nui + pr.block_ur - 1) / pr.block_ur;
+            pr.nbj = (pr.nuj + (1 << pr.block_ucs) - 1) >> pr.block_ucs;
+            n_blocks += (int64_t)pr.nbi * pr.nbj;
         }
-    } else {
-        // Few units per wave: longest first, each to the least-loaded wave.
-        // Units of one pair shape cost the same, so the list splits into a
-        // few groups of equal cost: unit g of a group goes to the wave at
-        // position g mod n_bins of the (load, index) order, i.e. every wave
-        // once per full round and the remainder to the least-loaded ones.
-        std::vector<PairCost> sorted(costs);
-        std::stable_sort(sorted.begin(), sorted.end(), [](const PairCost &x, const PairCost &y) { return x.c > y.c; });
-        std::vector<WorkItem> units((size_t)n_units);
-        std::vector<int32_t> unit_bin((size_t)n_units);
-        std::vector<double> load((size_t)n_bins, 0.0);
-        std::vector<int32_t> order((size_t)n_bins), merged((size_t)n_bins);
-        for (int b = 0; b < n_bins; ++b) order[b] = b;
-        auto before = [&](int32_t x, int32_t y) { return load[x] < load[y] || (load[x] == load[y] && x < y); };
-        int64_t k = 0;
-        size_t p0 = 0;
-        while (p0 < sorted.size()) {
-            size_t p1 = p0;
-            int64_t m_total = 0;
-            while (p1 < sorted.size() && sorted[p1].c == sorted[p0].c) m_total += sorted[p1++].n_units;
-            const double c = sorted[p0].c;
-            const int64_t full = m_total / n_bins, rem = m_total % n_bins;
-            int pos = 0;
-            for (size_t pp = p0; pp < p1; ++pp)
-                for (int32_t u = 0; u < sorted[pp].n_units; ++u, ++k) {
-                    units[k] = WorkItem{sorted[pp].pidx, u * (WAVE >> L.pairs[sorted[pp].pidx].tshift), 1, 0};
-                    unit_bin[k] = order[pos];
-                    if (++pos == n_bins) pos = 0;
-                }
-            for (int b = 0; b < n_bins; ++b) load[b] += c * full;
-            for (int64_t i = 0; i < rem; ++i) load[order[i]] += c;
-            if (rem > 0) {
-                // the first `rem` waves stay sorted among themselves after the
-                // increment, so one merge restores the order
-                std::merge(order.begin() + rem, order.end(), order.begin(), order.begin() + rem, merged.begin(), before);
-                order.swap(merged);
-            }
-            p0 = p1;
-        }
-        // group the units by wave (longest first inside each wave)
-        for (int64_t i = 0; i < n_units; ++i) ++L.bins[unit_bin[i] + 1];
-        for (int b = 0; b < n_bins; ++b) L.bins[b + 1] += L.bins[b];
-        L.work.resize((size_t)n_units);
-        std::vector<int32_t> fill(L.bins.begin(), L.bins.end() - 1);
-        for (int64_t i = 0; i < n_units; ++i) L.work[fill[unit_bin[i]]++] = units[i];
+        if ((double)n_blocks >= blocks_per_wave(L.family) * max_waves) break;
     }
-    L.bins[n_bins] = (int32_t)L.work.size();
+    // large plans: several blocks to a look, whose row's boxes are read once
+    L.strip_len = max_waves > 0 ? (int)std::max<int64_t>(1, std::min<int64_t>(MAX_STRIP, n_blocks / max_waves)) : 1;
+    int64_t n_strips = 0;
+    L.strip0.clear();
+    for (DPair &pr : L.pairs) {
+        pr.nsj = (pr.nbj + L.strip_len - 1) / L.strip_len;
+        pr.step_i = coprime_step(pr.nbi);
+        pr.step_j = coprime_step(pr.nsj);
+        L.strip0.push_back(n_strips);
+        n_strips += (int64_t)pr.nbi * pr.nsj;
+    }
+    L.strip0.push_back(n_strips);
+    constexpr int kWaves = K2_WG / WAVE;
+    const int64_t want_wg = (n_strips + kWaves - 1) / kWaves;
+    L.k2_grid = (int)std::min<int64_t>(want_wg, max_waves > 0 ? std::max(1, max_waves / kWaves) : INT_MAX);
 
     size_t off = 0;
     auto put = [&](size_t bytes) {
@@ -610,8 +531,7 @@ static void build_layout_once(const mhc_scene *scenes, int n_scenes, int variant
     L.o_pairs = put(L.pairs.size() * sizeof(DPair));
     L.o_polys = put(L.polys.size() * sizeof(DPoly));
     L.value_bytes = off;
-    L.o_work = put(L.work.size() * sizeof(WorkItem));
-    L.o_bins = put(L.bins.size() * sizeof(int32_t));
+    L.o_strip0 = put(L.strip0.size() * sizeof(int64_t));
     L.o_k1rows = put(L.k1_rows.size() * sizeof(int32_t));
     L.image_bytes = off;
     L.o_poses = put(L.pose_bytes);
@@ -711,6 +631,22 @@ void scene_origin(const mhc_scene &s, double *ox, double *oy)
     *oy = kOriginGrid * std::nearbyint((y0 / 2.0 + y1 / 2.0) / kOriginGrid);
 }
 
+// Half length and half width (about the tracked position) of a rectangle
+// around the object's shape, rounded up well above the FP32 rounding of the
+// extents that the tests use.
+static void half_extents(const mhc_object &o, float *hl, float *hw)
+{
+    double l = o.length / 2.0, w = o.width / 2.0;
+    if (o.kind != MHC_VEHICLE) l = w = o.radius;
+    if (o.n_vertices > 0) l = w = 0.0;
+    for (int e = 0; e < o.n_vertices; ++e) {
+        l = std::max(l, std::fabs(o.vertices[2 * e]));
+        w = std::max(w, std::fabs(o.vertices[2 * e + 1]));
+    }
+    *hl = (float)(l * (1.0 + 1e-6));
+    *hw = (float)(w * (1.0 + 1e-6));
+}
+
 void fill_values(const mhc_scene *scenes, int n_scenes, Layout &L)
 {
     size_t oi = 0, pi = 0, gi = 0;
@@ -727,6 +663,7 @@ void fill_values(const mhc_scene *scenes, int n_scenes, Layout &L)
             d.heading = o.heading;
             d.speed = o.speed;
             d.tau = s.dt;
+            half_extents(o, &d.hl, &d.hw);
             for (int k = 0; k < 6; ++k) d.params[k] = o.params[k];
             std::copy(o.u, o.u + o.n_u, L.vals.begin() + d.u_off);
             std::copy(o.w, o.w + o.n_w, L.vals.begin() + d.w_off);
@@ -763,8 +700,7 @@ void pack_image(const Layout &L, char *dst, bool values_only)
     cp(L.o_pairs, L.pairs.data(), L.pairs.size() * sizeof(DPair), L.o_polys);
     cp(L.o_polys, L.polys.data(), L.polys.size() * sizeof(DPoly), L.value_bytes);
     if (values_only) return;
-    cp(L.o_work, L.work.data(), L.work.size() * sizeof(WorkItem), L.o_bins);
-    cp(L.o_bins, L.bins.data(), L.bins.size() * sizeof(int32_t), L.o_k1rows);
+    cp(L.o_strip0, L.strip0.data(), L.strip0.size() * sizeof(int64_t), L.o_k1rows);
     cp(L.o_k1rows, L.k1_rows.data(), L.k1_rows.size() * sizeof(int32_t), L.image_bytes);
 }
 
@@ -774,12 +710,11 @@ Launch make_launch(const Layout &L, char *base, const mhc_result *dev_out, bool 
     X.objs = reinterpret_cast<const DObj *>(base + L.o_objs);
     X.vals = reinterpret_cast<const double *>(base + L.o_vals);
     X.pairs = reinterpret_cast<const DPair *>(base + L.o_pairs);
-    X.work = reinterpret_cast<const WorkItem *>(base + L.o_work);
     X.poses = base + L.o_poses;
     X.pfix = reinterpret_cast<unsigned long long *>(base + L.o_pfix);
     X.qacc = reinterpret_cast<unsigned long long *>(base + L.o_qacc);
     X.done = reinterpret_cast<unsigned long long *>(base + L.o_done);
-    X.bins = reinterpret_cast<const int32_t *>(base + L.o_bins);
+    X.strip0 = reinterpret_cast<const int64_t *>(base + L.o_strip0);
     X.k1_rows = L.k1_rows.empty() ? nullptr : reinterpret_cast<const int2 *>(base + L.o_k1rows);
     X.k1_nrows = L.k1_nrows;
     X.polys = reinterpret_cast<const DPoly *>(base + L.o_polys);
@@ -791,7 +726,6 @@ Launch make_launch(const Layout &L, char *base, const mhc_result *dev_out, bool 
     if (!keep_hits || !L.with_hits) X.hits = nullptr;
     X.timeline = L.timeline ? 1 : 0;
     X.one_track = L.one_track ? 1 : 0;
-    X.stage = L.stage ? 1 : 0;
     if (L.timeline) {
         X.hist = reinterpret_cast<unsigned long long *>(base + L.o_hist);
         X.att_w = reinterpret_cast<double *>(base + L.o_attw);
@@ -816,15 +750,17 @@ Launch make_launch(const Layout &L, char *base, const mhc_result *dev_out, bool 
     }
     X.n_obj = (int)L.objs.size();
     X.n_pairs = (int)L.pairs.size();
-    X.n_work = (int)L.work.size();
+    X.n_strips = L.strip0.back();
+    X.strip_len = L.strip_len;
+    X.side_shift = L.side_shift;
+    X.n_hits = L.n_hits;
+    X.k2_grid = L.k2_grid;
     X.k1_x = L.k1_x;
     X.k3_x = L.k3_x;
     X.k3t_x = (int)L.k3t_x;
     X.k4t_y = L.k4t_y;
     X.variant = L.variant;
     X.family = L.family;
-    X.n_bins = (int)L.bins.size() - 1;
-    X.xcd_major = L.contiguous ? 1 : 0;
     (void)n_cu;
     return X;
 }
@@ -913,19 +849,11 @@ int mhc_ctx::max_waves(int v, const mhc_scene *scenes, int n)
     return max_waves_of(v, fam, tl != 0);
 }
 
-int mhc_ctx::max_waves_staged(int v, const mhc_scene *scenes, int n)
-{
-    for (int k = 0; k < n; ++k)
-        if (scene_family(&scenes[k]) != FAM_PLAIN || scenes[k].timeline) return 0;
-    return max_waves_of(v, FAM_PLAIN, false, true);
-}
-
-int mhc_ctx::max_waves_of(int v, int fam, bool tl, bool stage)
+int mhc_ctx::max_waves_of(int v, int fam, bool tl)
 {
     if (v < 0 || v >= N_VARIANTS) v = 0;
-    stage = stage && fam == FAM_PLAIN && !tl;
-    int &w = waves_cache[v][fam][tl ? 1 : 0][stage ? 1 : 0];
-    if (!w) w = n_cu * collide_blocks_per_cu(v, fam, tl, stage) * (WG / WAVE);
+    int &w = waves_cache[v][fam][tl ? 1 : 0];
+    if (!w) w = n_cu * collide_blocks_per_cu(v, fam, tl, true);
     return w;
 }
 
@@ -953,88 +881,95 @@ extern "C" mhc_status mhc_query_sizes(const mhc_scene *scene, mhc_sizes *out)
     return MHC_OK;
 }
 
-// Walks a collision plan the way k2_collide decodes it: wave slot -> segments
-// -> units -> lanes -> items -> trajectory pairs and steps, counting how often
-// each item is tested and every index that leaves its pair.
+// Walks a collision plan the way k2_collide decodes it: rounds -> workgroups ->
+// waves -> strips -> blocks -> units -> lanes -> items -> trajectory pairs, counting how
+// often each item is tested and every index that leaves its pair.
 static void walk_plan(const Layout &L, mhc_plan_info &info)
 {
     std::vector<int64_t> item_base(L.pairs.size() + 1, 0);
     for (size_t p = 0; p < L.pairs.size(); ++p)
         item_base[p + 1] = item_base[p] + (int64_t)L.pairs[p].n_ig * L.pairs[p].n_jg;
     std::vector<uint8_t> seen((size_t)item_base.back(), 0);
-    const int n_bins = (int)L.bins.size() - 1;
     int64_t bad = 0, units = 0;
     int32_t time_split = 1;
-    if (n_bins < 1 || L.bins[0] != 0 || L.bins[n_bins] != (int32_t)L.work.size()) ++bad;
-    for (int b = 0; b < n_bins && !bad; ++b) {
-        if (L.bins[b + 1] < L.bins[b]) {
-            ++bad;
-            break;
+    if (L.strip0.size() != L.pairs.size() + 1 || L.strip0[0] != 0 || L.k2_grid < 1) ++bad;
+    for (size_t p = 0; p < L.pairs.size() && !bad; ++p) {
+        const DPair &pr = L.pairs[p];
+        const TileShape ts = kTiles[L.variant][pr.cls];
+        // every position of an object holds another of its trajectories
+        for (const DObj *o : {&L.objs[pr.a], &L.objs[pr.b]}) {
+            std::vector<uint8_t> held((size_t)o->T, 0);
+            for (int k = 0; k < o->T; ++k) {
+                const int i = traj_at(k, o->n_u, o->n_w, o->strip);
+                if (i < 0 || i >= o->T || held[(size_t)i]++) ++bad;
+            }
         }
-        for (int32_t wi = L.bins[b]; wi < L.bins[b + 1]; ++wi) {
-            const WorkItem &w = L.work[wi];
-            if (w.pair < 0 || w.pair >= (int32_t)L.pairs.size() || w.n_units < 0) {
-                ++bad;
-                continue;
-            }
-            const DPair &pr = L.pairs[w.pair];
-            const int per = WAVE >> pr.tshift;
-            const int chunk = split_chunk(pr.H, pr.tshift);
+        // the units tile the items, the blocks the units, and a block's leaves
+        // hold its units' positions
+        if (pr.tshift < 0 || pr.tshift > MAX_TSHIFT || pr.bshift < 0 || pr.bshift > 6 - pr.tshift ||
+            (1 << pr.tshift) > pr.H || L.strip0[p + 1] - L.strip0[p] != (int64_t)pr.nbi * pr.nsj) {
+            ++bad;
+            continue;
+        }
+        const int rows = (WAVE >> pr.tshift) >> pr.bshift, cols = 1 << pr.bshift;
+        if ((int64_t)pr.nui * rows < pr.n_ig || (int64_t)pr.nuj * cols < pr.n_jg || pr.nbi * pr.block_ur < pr.nui ||
+            (pr.nbj << pr.block_ucs) < pr.nuj || pr.block_ur * rows * ts.ri != (1 << L.side_shift) ||
+            (cols * ts.rj) << pr.block_ucs != (1 << L.side_shift) || 1 << pr.unit_rs != rows * ts.ri ||
+            1 << pr.unit_cs != cols * ts.rj || rows * ts.ri > BLOCK_SIDE || cols * ts.rj > BLOCK_SIDE || (pr.nbi - 1) * (1 << L.side_shift) >= pr.Ta ||
+            (pr.nbj - 1) * (1 << L.side_shift) >= pr.Tb || pr.nsj * L.strip_len < pr.nbj ||
+            (pr.nsj - 1) * L.strip_len >= pr.nbj || 1 << L.side_shift > BLOCK_SIDE ||
+            (pr.block_ur << pr.block_ucs) * MIN_UNIT_PAIRS > BLOCK_PAIRS)
+            ++bad;
+        time_split = std::max(time_split, 1 << pr.tshift);
+    }
+    const int64_t n_strips = bad ? 0 : L.strip0.back();
+    const int64_t per_round = (int64_t)L.k2_grid * (K2_WG / WAVE);
+    const int64_t rounds = (n_strips + per_round - 1) / std::max<int64_t>(1, per_round);
+    for (int64_t rw = 0; rw < rounds * (K2_WG / WAVE) && !bad; ++rw)
+        for (int wg = 0; wg < L.k2_grid; ++wg) {
+            const int64_t g = rw * L.k2_grid + strip_in_row((int)rw, wg, L.k2_grid);
+            if (g >= n_strips) continue;
+            const size_t p = (size_t)(std::upper_bound(L.strip0.begin(), L.strip0.end(), g) - L.strip0.begin()) - 1;
+            const DPair &pr = L.pairs[p];
             const TileShape ts = kTiles[L.variant][pr.cls];
-            const int ri = ts.ri, rj = ts.rj;
-            if (pr.tshift < 0 || pr.tshift > MAX_TSHIFT || w.item0 % per != 0) ++bad;
-            // the parts' step ranges: inside [0, H), the first from 0, the
-            // last to H, each starting at or before the end of the one before
-            for (int part = 0, end = 0; part < (1 << pr.tshift); ++part) {
-                const int t0 = std::min(part * chunk, pr.H - chunk);
-                if (t0 < 0 || t0 > end || t0 + chunk > pr.H) ++bad;
-                end = t0 + chunk;
-                if (part == (1 << pr.tshift) - 1 && end != pr.H) ++bad;
-            }
-            time_split = std::max(time_split, 1 << pr.tshift);
-            const int64_t n_units = pair_units(pr, pr.tshift, pr.bshift);
-            for (int32_t u = 0; u < w.n_units; ++u) {
+            const DObj &oa = L.objs[pr.a], &ob = L.objs[pr.b];
+            const int ri = ts.ri, rj = ts.rj, per = WAVE >> pr.tshift;
+            int bi, sj;
+            strip_at(pr, (uint32_t)(g - L.strip0[p]), &bi, &sj);
+            if (bi < 0 || bi >= pr.nbi || sj < 0 || sj >= pr.nsj) ++bad;
+            const int units_of = pr.block_ur << pr.block_ucs;
+            for (int x = 0; x < units_of * L.strip_len; ++x) {
+                const int bj = sj * L.strip_len + x / units_of, u = x % units_of;
+                if (bj >= pr.nbj) break;
+                const int ui = bi * pr.block_ur + (u >> pr.block_ucs);
+                const int uj = (bj << pr.block_ucs) + (u & ((1 << pr.block_ucs) - 1));
+                if (ui >= pr.nui || uj >= pr.nuj) continue;
                 ++units;
-                const int64_t item0 = (int64_t)w.item0 + (int64_t)u * per;
-                const int64_t v = item0 / per;
-                if (v >= n_units) ++bad;
-                for (int lane = 0; lane < WAVE; ++lane) {
-                    const int part = lane >> (6 - pr.tshift);
-                    const int e = lane & (per - 1);
-                    int64_t ig, jg;
-                    if (pr.bshift == 0) {
-                        const int64_t f = item0 + e;
-                        if (f >= (int64_t)pr.n_ig * pr.n_jg) continue;
-                        ig = f / pr.n_jg;
-                        jg = f - ig * pr.n_jg;
-                    } else {
-                        const int bs = pr.bshift;
-                        const int64_t nb = (pr.n_jg + (1 << bs) - 1) >> bs;
-                        const int64_t bi = v / nb;
-                        ig = ((bi << (6 - pr.tshift)) >> bs) + (e >> bs);
-                        jg = ((v - bi * nb) << bs) + (e & ((1 << bs) - 1));
-                        if (ig >= pr.n_ig || jg >= pr.n_jg) continue;
-                    }
+                for (int lane = 0; lane < per; ++lane) {   // the lanes of part 0
+                    const int ig = ui * (per >> pr.bshift) + (lane >> pr.bshift);
+                    const int jg = (uj << pr.bshift) + (lane & ((1 << pr.bshift) - 1));
+                    if (ig >= pr.n_ig || jg >= pr.n_jg) continue;
                     if (ig < 0 || jg < 0) {
                         ++bad;
                         continue;
                     }
                     for (int r = 0; r < ri; ++r)
                         for (int sidx = 0; sidx < rj; ++sidx) {
-                            const int64_t i = ig + (int64_t)r * pr.n_ig, j = jg + (int64_t)sidx * pr.n_jg;
-                            if (i >= pr.Ta || j >= pr.Tb) continue;  // idle tile slot
+                            const int64_t pi = (int64_t)ig * ri + r, pj = (int64_t)jg * rj + sidx;
+                            if (pi >= pr.Ta || pj >= pr.Tb) continue;  // idle tile slot
+                            const int64_t i = traj_at((int)pi, oa.n_u, oa.n_w, oa.strip);
+                            const int64_t j = traj_at((int)pj, ob.n_u, ob.n_w, ob.strip);
                             const int64_t h = pr.hit_off + i * pr.Tb + j;
                             if (h < 0 || h >= L.n_hits) ++bad;
-                            if (pr.qa0 + i * pr.qn >= L.n_q || pr.qb0 + j * pr.qn >= L.n_q) ++bad;
+                            if (oa.q_row + i * oa.n_scene_obj + ob.local >= L.n_q ||
+                                ob.q_row + j * ob.n_scene_obj + oa.local >= L.n_q)
+                                ++bad;
                         }
-                    if (part == 0) {
-                        uint8_t &c = seen[(size_t)(item_base[w.pair] + ig * pr.n_jg + jg)];
-                        if (c < 255) ++c;
-                    }
+                    uint8_t &s = seen[(size_t)(item_base[p] + (int64_t)ig * pr.n_jg + jg)];
+                    if (s < 255) ++s;
                 }
             }
         }
-    }
     int64_t uncovered = 0, repeated = 0;
     for (uint8_t c : seen) {
         uncovered += c == 0;
@@ -1067,12 +1002,12 @@ static void walk_plan(const Layout &L, mhc_plan_info &info)
     int64_t blocked = 0;
     for (const DPair &pr : L.pairs) blocked += pr.bshift != 0;
     info.n_units = units;
-    info.n_waves = n_bins;
+    info.n_waves = per_round;
     info.blocked_pairs = blocked;
     info.uncovered = uncovered;
     info.repeated = repeated;
     info.out_of_range = bad;
-    info.contiguous = L.contiguous ? 1 : 0;
+    info.contiguous = rounds > 1 ? 1 : 0;
     info.time_split = time_split;
 }
 
@@ -1136,7 +1071,7 @@ static bool layout_for(mhc_ctx *ctx, const mhc_scene *scene, Layout &L, bool wit
         fill_values(scene, 1, L);
         return true;
     }
-    build_layout(scene, 1, v, ctx->max_waves(v, scene, 1), L, with_hits, ctx->max_waves_staged(v, scene, 1));
+    build_layout(scene, 1, v, ctx->max_waves(v, scene, 1), L, with_hits, ctx->budget ? ctx->budget : SIZE_MAX);
     ctx->layout_shape = std::move(shape);
     return false;
 }
@@ -1421,7 +1356,7 @@ extern "C" mhc_status mhc_evaluate_async(mhc_ctx *ctx, const mhc_scene *scene, v
     if (!validate_scene(scene, ctx->err) || !validate_outputs(scene, dev_out, ctx->err)) return MHC_E_INVAL;
     Layout L;
     const int v = ctx->variant_for(scene, 1);
-    build_layout(scene, 1, v, ctx->max_waves(v, scene, 1), L, true, ctx->max_waves_staged(v, scene, 1));
+    build_layout(scene, 1, v, ctx->max_waves(v, scene, 1), L, true, workspace_bytes);
     if (workspace_bytes < L.total_bytes) {
         ctx->err = "workspace too small: need " + std::to_string(L.total_bytes) + " bytes";
         return MHC_E_INVAL;
@@ -1448,7 +1383,7 @@ extern "C" mhc_status mhc_evaluate_noalloc(mhc_ctx *ctx, const mhc_scene *scene,
     // the first hits go to dev_out->first_hit only, so the array holds none
     Layout &L = ctx->noalloc_layout;
     const int v = ctx->variant_for(scene, 1);
-    build_layout(scene, 1, v, ctx->max_waves(v, scene, 1), L, false, ctx->max_waves_staged(v, scene, 1));
+    build_layout(scene, 1, v, ctx->max_waves(v, scene, 1), L, false, kNoallocBytes);
     if (L.total_bytes > kNoallocBytes) {
         ctx->err = "scene needs " + std::to_string(L.total_bytes) + " workspace bytes, above MHC_NOALLOC_MAX_BYTES (" +
                    std::to_string(kNoallocBytes) + ")";
@@ -1565,7 +1500,7 @@ extern "C" mhc_status mhc_plan_create(mhc_ctx *ctx, const mhc_scene *scene, mhc_
     mhc_plan *pl = new mhc_plan();
     pl->ctx = ctx;
     const int v = ctx->variant_for(scene, 1);
-    build_layout(scene, 1, v, ctx->max_waves(v, scene, 1), pl->L, true, ctx->max_waves_staged(v, scene, 1));
+    build_layout(scene, 1, v, ctx->max_waves(v, scene, 1), pl->L, true, ctx->budget ? ctx->budget : SIZE_MAX);
     pl->shape = shape_of(scene);
     pl->flags = *scene;
     pl->flags.objects = nullptr;
@@ -1602,8 +1537,7 @@ extern "C" mhc_status mhc_plan_update(mhc_plan *pl, const mhc_scene *scene)
     }
     HIPC(hipSetDevice(ctx->device));
     Layout L;
-    build_layout(scene, 1, pl->L.variant, ctx->max_waves(pl->L.variant, scene, 1), L, true,
-                 ctx->max_waves_staged(pl->L.variant, scene, 1));
+    build_layout(scene, 1, pl->L.variant, ctx->max_waves(pl->L.variant, scene, 1), L, true, pl->L.total_bytes);
     std::vector<char> img(L.image_bytes);
     pack_image(L, img.data());
     HIPC(hipDeviceSynchronize());
@@ -1656,6 +1590,7 @@ extern "C" mhc_status mhc_plan_execute_stages(mhc_plan *pl, const mhc_result *de
     const hipStream_t s = static_cast<hipStream_t>(hip_stream);
     Launch X = make_launch(pl->L, pl->dbuf, dev_out, true, ctx->n_cu);
     if (stages & MHC_STAGE_TRAJ) HIPC(launch_trajgen(X, s));
+    X.clear_hits = !(stages & MHC_STAGE_TRAJ);
     if (stages & MHC_STAGE_COLLIDE) HIPC(launch_collide(X, s));
     if (stages & MHC_STAGE_RISK) HIPC(launch_risk(X, s));
     return MHC_OK;
@@ -1718,7 +1653,7 @@ extern "C" mhc_status mhc_evaluate_batch(mhc_ctx *ctx, int32_t n, const mhc_scen
 }
 
 // Batched form: all scenes share one scene image, one trajectory launch, one
-// collision launch over a longest-first work list and one risk launch.
+// collision launch over all their pairs' units and one risk launch.
 mhc_status batch_run(mhc_ctx *ctx, int n, const mhc_scene *scenes, mhc_result *res)
 {
     Layout &L = ctx->layout;
@@ -1742,7 +1677,7 @@ mhc_status batch_run(mhc_ctx *ctx, int n, const mhc_scene *scenes, mhc_result *r
     if (reused) {
         fill_values(scenes, n, L);
     } else {
-        build_layout(scenes, n, v, waves, L, keep, ctx->max_waves_staged(v, scenes, n));
+        build_layout(scenes, n, v, waves, L, keep, ctx->budget ? ctx->budget : SIZE_MAX);
         ctx->layout_shape = std::move(shape);
     }
     mhc_status st = ensure_device(ctx, L.total_bytes);

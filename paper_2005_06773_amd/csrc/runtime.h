@@ -40,8 +40,11 @@ struct Layout {
     std::vector<DObj> objs;
     std::vector<double> vals;
     std::vector<DPair> pairs;
-    std::vector<WorkItem> work;     // grouped by collision wave
-    std::vector<int32_t> bins;       // [n_bins+1] range of each collision wave in `work`
+    std::vector<int64_t> strip0;     // [n_pairs+1] first strip of collision blocks of each pair
+    int64_t n_units = 0;             // collision units
+    int strip_len = 1;               // blocks of a strip
+    int side_shift = 0;              // log2 of the positions to a side of a block
+    int k2_grid = 0;                 // workgroups of the collision kernel
     std::vector<DPoly> polys;        // polygons of the polygon pairs
     std::vector<SceneExt> sc;
     std::vector<int32_t> k1_rows;    // trajectory kernel rows (object, first block) when objects differ in size
@@ -54,17 +57,15 @@ struct Layout {
     int64_t k3t_x = 0;            // time-resolved risk kernel grid x (one wave of lanes of the largest object per workgroup)
     int k4t_y = 0;                // time-resolved reduction grid y (rows: slots + objects)
     size_t pose_bytes = 0;
-    size_t o_objs = 0, o_vals = 0, o_pairs = 0, o_work = 0, o_bins = 0, o_k1rows = 0, o_polys = 0, image_bytes = 0;
+    size_t o_objs = 0, o_vals = 0, o_pairs = 0, o_strip0 = 0, o_k1rows = 0, o_polys = 0, image_bytes = 0;
     size_t value_bytes = 0;       // the image's leading part that fill_values rewrites (before the plan)
     size_t o_poses = 0, o_pfix = 0, o_qacc = 0, o_done = 0, o_p = 0, o_hits = 0, o_q = 0, o_tc = 0, o_oc = 0;
     size_t o_hist = 0, o_attw = 0, o_ctw = 0, o_ct = 0, o_tct = 0, o_at = 0, o_tat = 0, total_bytes = 0;
     int variant = 0;
-    bool contiguous = false;      // collision plan of contiguous stretches
     int family = 0;               // ClassFamily covering every pair
     bool with_hits = true;        // the workspace holds the first-hit matrix
     bool one_track = false;       // some object follows the one-track model
-    bool stage = false;           // the collision launch uses the LDS-staged instance
-    double staged_share = 0.0;    // share of the collision cost in 8 x 8 blocks without a time split
+    bool boxes = true;            // the workspace holds the leaves' boxes (else every step is tested)
 };
 
 // Instantiated HIP graphs keyed by what their launch sequence depends on.
@@ -96,20 +97,15 @@ bool validate_outputs(const mhc_scene *s, const mhc_result *r, std::string &err,
 // Test class (CLS_*) of an object pair of kinds ka, kb under an overlap mode,
 // given whether each has an outline.
 int pair_class(int ka, int kb, int overlap, bool outline_a, bool outline_b);
-// Relative VALU cost of one test of a class (k_a, k_b: polygon vertex counts).
-double class_cost(int cls, int k_a, int k_b);
 bool outline_ok(int k, const double *v);
 bool scene_has_outline(const mhc_scene *s);
 // The class family a scene needs (ClassFamily).
 int scene_family(const mhc_scene *s);
 // max_waves: resident waves of the collision kernel (0 = one per work unit).
-// When the plan's 8 x 8 item blocks without a time split carry at least half
-// its cost (plain class family, no risk over time), the launch uses the
-// collision instance that stages them in LDS, and the plan is made for that
-// instance's resident waves, max_waves_staged (0: the same as max_waves).
-// max_tshift caps the time split of the plan's units (S <= 2^max_tshift).
+// max_bytes: where the workspace would exceed it, it is laid out without the
+// leaves' boxes (the collision kernel then tests every step; same results).
 void build_layout(const mhc_scene *scenes, int n_scenes, int variant, int max_waves, Layout &L, bool with_hits,
-                  int max_waves_staged = 0, int max_tshift = MAX_TSHIFT);
+                  size_t max_bytes = SIZE_MAX);
 
 // The host side of the results of the n scenes of a layout: per output, the
 // workspace range [lo, hi) of every requested part and, where staged, its
@@ -177,13 +173,11 @@ struct mhc_ctx {
     mhc::GraphCache batch_graphs;                 // mhc_evaluate_batch, keyed by batch shape
     mhc::Tuning tune;
     int variant_for(const mhc_scene *scenes, int n) const { return tune.variant_for(scenes, n); }
-    int waves_cache[mhc::N_VARIANTS][3][2][2] = {};  // [variant][class family][time-resolved][staged]
+    int waves_cache[mhc::N_VARIANTS][3][2] = {};  // [variant][class family][time-resolved]
     // resident waves on this GPU of the collision kernel that `scenes` need
-    // (of its LDS-staged instance: max_waves_staged, 0 where there is none)
     int max_waves(int variant, const mhc_scene *scenes, int n);
-    int max_waves_staged(int variant, const mhc_scene *scenes, int n);
-    // the same for a variant, class family, time-resolved flag and staging
-    int max_waves_of(int variant, int family, bool timeline, bool stage = false);
+    // the same for a variant, class family and time-resolved flag
+    int max_waves_of(int variant, int family, bool timeline);
 };
 
 // Autotuning class of a launch: log2 of the mean trajectory count, log2 of

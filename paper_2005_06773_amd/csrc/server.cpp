@@ -65,12 +65,9 @@ std::chrono::system_clock::time_point wait_deadline(std::chrono::microseconds d)
     return std::chrono::system_clock::now() + d;
 }
 
-// Bound on the resident collision waves of any GPU this library runs on
-// (sizes the slot table in the admission estimate).
-constexpr int kMaxCollisionWaves = 1 << 16;
-// Ticks split collision units in time into at most 4 parts: the admission
-// bound counts a collision segment per unit of 16 items.
-constexpr int kTickMaxTshift = 2;
+// Bytes of a slot that admission leaves out: what a tick's tables may take
+// beyond those of its frames.
+constexpr size_t kTickReserve = ((size_t)1 << 18) + 256;
 constexpr int64_t kDefaultWatchdogUs = 30LL * 1000 * 1000;
 
 enum FrameState { QUEUED, ADMITTED, DONE };
@@ -86,6 +83,7 @@ struct Frame {
     int64_t n_traj = 0, n_hits = 0, checks = 0;
     size_t bytes = 0;    // device bytes upper bound
     bool large = false;  // more checks than one tick may carry
+    bool boxes_optional = false;  // pedestrians' trajectories outnumber vehicles' by more than 7 to 1
     FrameState state = QUEUED;
     mhc_status status = MHC_OK;
     mhc_timing timing{};
@@ -172,7 +170,6 @@ public:
     int64_t max_checks_per_tick = 0;
     Tuning tune;
     int waves[N_VARIANTS][3][2] = {};
-    int waves_staged[N_VARIANTS] = {};   // of the LDS-staged instances (plain family, no per-slot sums)
     std::vector<TickSlot> slots;
 
     int max_waves(int v, const mhc_scene *scenes, int n) const
@@ -220,14 +217,8 @@ public:
         // for the other slots' kernels while it runs
         const bool large = checks > max_checks_per_tick;
         int waves_v = max_waves(v, scenes.data(), n);
-        bool plain = true;
-        for (int k = 0; k < n; ++k) plain &= scene_family(&scenes[k]) == FAM_PLAIN && !scenes[k].timeline;
-        int waves_s = plain ? waves_staged[v] : 0;
-        if (large) {
-            waves_v = std::max(1, waves_v / 5 * 4);
-            waves_s = waves_s / 5 * 4;
-        }
-        build_layout(scenes.data(), n, v, waves_v, t.L, keep_hits, waves_s, kTickMaxTshift);
+        if (large) waves_v = std::max(1, waves_v / 5 * 4);
+        build_layout(scenes.data(), n, v, waves_v, t.L, keep_hits, t.dbytes);
         if (t.L.total_bytes > t.dbytes) {  // the admission bound excludes this
             err = "tick workspace above the slot's share of the budget";
             return MHC_E_NOMEM;
@@ -372,7 +363,7 @@ struct mhc_server {
     std::unique_ptr<Executor> exec;
     mhc_server_cfg cfg{};
     size_t slot_bytes = 0;
-    size_t slot_usable = 0;   // slot bytes minus the per-tick collision slot table
+    size_t slot_usable = 0;   // slot bytes minus kTickReserve
     std::vector<Slot> slots;
     std::thread thread;
     std::mutex mu;
@@ -391,48 +382,32 @@ struct mhc_server {
 namespace {
 
 // Upper bound of the device bytes a frame adds to a tick (every buffer of the
-// workspace layout, with one collision segment per work unit).
-void frame_sizes(const mhc_scene *s, int max_waves, bool hits, Frame &f)
+// workspace layout), with or without the leaves' boxes.
+void frame_sizes(const mhc_scene *s, bool hits, bool boxes, Frame &f)
 {
-    int64_t n_traj = 0, pose = 0, n_units = 0, n_hits = 0, vals = 0, n_pairs = 0, k1_blocks = 0;
+    int64_t n_traj = 0, n_ped = 0, pose = 0, n_hits = 0, vals = 0, n_pairs = 0, k1_blocks = 0;
     const int n = s->n_objects;
     for (int a = 0; a < n; ++a) {
         const int64_t T = (int64_t)s->objects[a].n_u * s->objects[a].n_w;
         n_traj += T;
-        // poses; a vehicle's frame block beside them
         const bool vehicle = s->objects[a].kind == MHC_VEHICLE;
-        pose += align256((size_t)s->horizon * T * (vehicle ? 16 : 8)) * (vehicle ? 2 : 1);
+        n_ped += vehicle ? 0 : T;
+        pose += align256((size_t)s->horizon * T * (vehicle ? 16 : 8));
+        if (boxes) pose += align256((size_t)s->horizon * ((T + LEAF - 1) / LEAF) * sizeof(float4));
         vals += s->objects[a].n_u + s->objects[a].n_w + (s->objects[a].score ? T : 0);
         k1_blocks += (T + K1_TPB - 1) / K1_TPB + 1;
     }
     for (int a = 0; a < n; ++a)
         for (int b = a + 1; b < n; ++b) {
             if (s->pairs == MHC_PAIRS_EGO && a != 0) continue;
-            const int64_t Ta = (int64_t)s->objects[a].n_u * s->objects[a].n_w;
-            const int64_t Tb = (int64_t)s->objects[b].n_u * s->objects[b].n_w;
-            n_hits += Ta * Tb;
-            // one collision segment per work unit, for the variant and the
-            // time split (a tick's: up to 4 parts, 16 items a unit) that cut
-            // this pair into the most units (2-D blocks of items are taken
-            // where they add at most 1/32 to the units of the row-major cut)
-            const bool poly = scene_has_outline(s);
-            const int cls = pair_class(s->objects[a].kind, s->objects[b].kind, s->overlap,
-                                       poly && s->objects[a].n_vertices > 0, poly && s->objects[b].n_vertices > 0);
-            int64_t most = 0;
-            for (int v = 0; v < N_VARIANTS; ++v) {
-                const int64_t items = (Ta + kTiles[v][cls].ri - 1) / kTiles[v][cls].ri *
-                                      ((Tb + kTiles[v][cls].rj - 1) / kTiles[v][cls].rj);
-                const int64_t per = WAVE >> kTickMaxTshift;
-                most = std::max(most, ((items + per - 1) / per * 33 + 31) / 32);
-            }
-            n_units += most;
+            n_hits += (int64_t)s->objects[a].n_u * s->objects[a].n_w * s->objects[b].n_u * s->objects[b].n_w;
             ++n_pairs;
         }
     const int64_t n_q = n_traj * n;
     size_t bytes = 0;
     bytes += align256(n * sizeof(DObj)) + align256(vals * 8) + align256(n_pairs * sizeof(DPair));
     bytes += align256((scene_has_outline(s) ? n : 0) * sizeof(DPoly));
-    bytes += align256((n_units + 1) * sizeof(WorkItem));
+    bytes += align256((n_pairs + 1) * sizeof(int64_t));   // first strip of each pair
     bytes += align256(k1_blocks * 2 * sizeof(int32_t));  // trajectory kernel rows (at most one per block)
     bytes += pose + align256(n_traj * 8) * 3 + align256(n_q * 8) * 2;  // p*2^62, p, traj crit; q sums, q
     bytes += align256(n * 8);                                            // risk kernel's per-object words
@@ -448,7 +423,7 @@ void frame_sizes(const mhc_scene *s, int max_waves, bool hits, Frame &f)
                  align256((size_t)n * n * 8);
     }
     bytes += 16 * 256;                              // alignment slack of the tables
-    bytes += align256(((size_t)max_waves + 1) * 4);  // the collision plan's slot table
+    f.boxes_optional = n_ped > 7 * (n_traj - n_ped);
     f.n_traj = n_traj;
     f.n_hits = n_hits;
     f.checks = n_hits * s->horizon;
@@ -654,13 +629,12 @@ mhc_server *new_server(const mhc_server_cfg &c, std::string &err)
     auto *srv = new mhc_server();
     srv->cfg = c;
     srv->slot_bytes = (c.hbm_budget_bytes / c.max_inflight_ticks) & ~size_t(255);
-    const size_t table = align256(((size_t)kMaxCollisionWaves + 1) * 4);
-    if (srv->slot_bytes <= 2 * table) {
+    if (srv->slot_bytes <= 2 * kTickReserve) {
         err = "server budget too small";
         delete srv;
         return nullptr;
     }
-    srv->slot_usable = srv->slot_bytes - table;
+    srv->slot_usable = srv->slot_bytes - kTickReserve;
     srv->slots.resize(c.max_inflight_ticks);
     return srv;
 }
@@ -695,7 +669,6 @@ extern "C" mhc_status mhc_server_start(mhc_ctx *ctx, const mhc_server_cfg *cfg, 
     for (int v = 0; v < N_VARIANTS; ++v)
         for (int fam = 0; fam < 3; ++fam)
             for (int tl = 0; tl < 2; ++tl) ex->waves[v][fam][tl] = ctx->max_waves_of(v, fam, tl != 0);
-    for (int v = 0; v < N_VARIANTS; ++v) ex->waves_staged[v] = ctx->max_waves_of(v, FAM_PLAIN, false, true);
     ex->slots.resize(c.max_inflight_ticks);
     for (auto &t : ex->slots) {
         if (hipStreamCreateWithFlags(&t.stream, hipStreamNonBlocking) != hipSuccess ||
@@ -749,7 +722,10 @@ extern "C" mhc_status mhc_submit(mhc_server *srv, int32_t stream_id, const mhc_s
     if (!dst || !dst->object_crit || !validate_outputs(scene, dst, err)) return MHC_E_INVAL;
     auto f = copy_frame(scene);
     f->dst = *dst;
-    frame_sizes(&f->scene, 0, dst->first_hit != nullptr, *f);
+    frame_sizes(&f->scene, dst->first_hit != nullptr, true, *f);
+    // a frame of pedestrians mostly, whose boxes take a quarter of their poses
+    // (vehicles': an eighth), runs without them where it fits a slot only so
+    if (f->bytes > srv->slot_usable && f->boxes_optional) frame_sizes(&f->scene, dst->first_hit != nullptr, false, *f);
     f->large = f->checks > srv->cfg.max_checks_per_tick;
     f->stream_id = stream_id;
     f->timing.submit_ns = now_ns();

@@ -96,7 +96,7 @@ static mhc_status tune_scenes(mhc_ctx *ctx, int n, const mhc_scene *scenes, int3
     std::vector<size_t> off(N_VARIANTS);
     size_t total = 0;
     for (int v = 0; v < N_VARIANTS; ++v) {
-        build_layout(scenes, n, v, ctx->max_waves(v, scenes, n), Ls[v], false, ctx->max_waves_staged(v, scenes, n));
+        build_layout(scenes, n, v, ctx->max_waves(v, scenes, n), Ls[v], false, ctx->budget ? ctx->budget : SIZE_MAX);
         off[v] = total;
         total += (Ls[v].total_bytes + 255) & ~(size_t)255;
     }
