@@ -661,8 +661,26 @@ struct CheckPP : PrepNone {
 //     one has n_e.x <= h_e for every edge of the other.
 // Both read the same vertex-edge values. Polygons come padded to KP, KQ = 4
 // or 8 vertices (repeated vertices and edges change none of the tests), so
-// the loops are straight-line code; their constants are read from the wave's
-// copy of the two polygons in LDS.
+// loop lengths are known; their constants are read from the wave's copy of the
+// two polygons in LDS, an edge's in two 16-byte words. The separating-axis
+// tests are bound by instruction issue and, with one edge at a time, by the LDS
+// latency of each. Collision kernel on the octagon scene, mean of four scenes: a
+// comparison per vertex and edge 80 us, the least of an edge's values against
+// its offset instead 65, the words of two edges read together 51 (four: the
+// same; all eight: spills), giving up between the two polygons' edges 49.
+
+// Whether every one of K points lies beyond an edge, n.x > h: the least of them
+// does (a minimum that keeps NaNs, which lie beyond nothing).
+template <int K>
+__device__ __forceinline__ bool beyond(const DEdge &E, const float (&x)[K], const float (&y)[K])
+{
+    const float nx = E.nx, ny = E.ny;
+    float least = fmaf(nx, x[0], ny * y[0]);
+#pragma unroll
+    for (int v = 1; v < K; ++v) least = __builtin_elementwise_minimum(least, fmaf(nx, x[v], ny * y[v]));
+    return least > E.h;
+}
+
 template <int KP, int KQ, bool PIPMODE>
 struct CheckGG : PrepNone {
     const DPoly *P, *Q;   // LDS
@@ -680,32 +698,21 @@ struct CheckGG : PrepNone {
         float qx[KQ], qy[KQ], px[KP], py[KP];
 #pragma unroll
         for (int v = 0; v < KQ; ++v) {
-            qx[v] = fmaf(Q->vx[v], C, fmaf(-Q->vy[v], S, lam));
-            qy[v] = fmaf(Q->vx[v], S, fmaf(Q->vy[v], C, mu));
+            qx[v] = fmaf(Q->edge[v].vx, C, fmaf(-Q->edge[v].vy, S, lam));
+            qy[v] = fmaf(Q->edge[v].vx, S, fmaf(Q->edge[v].vy, C, mu));
         }
 #pragma unroll
         for (int v = 0; v < KP; ++v) {
-            px[v] = fmaf(P->vx[v], C, fmaf(P->vy[v], S, lam2));
-            py[v] = fmaf(-P->vx[v], S, fmaf(P->vy[v], C, mu2));
+            px[v] = fmaf(P->edge[v].vx, C, fmaf(P->edge[v].vy, S, lam2));
+            py[v] = fmaf(-P->edge[v].vx, S, fmaf(P->edge[v].vy, C, mu2));
         }
         if constexpr (!PIPMODE) {
             bool sep = false;
-#pragma unroll 1
-            for (int e = 0; e < KP; ++e) {
-                const float nx = P->nx[e], ny = P->ny[e], h = P->h[e];
-                bool out = true;
-#pragma unroll
-                for (int v = 0; v < KQ; ++v) out &= fmaf(nx, qx[v], ny * qy[v]) > h;
-                sep |= out;
-            }
-#pragma unroll 1
-            for (int e = 0; e < KQ; ++e) {
-                const float nx = Q->nx[e], ny = Q->ny[e], h = Q->h[e];
-                bool out = true;
-#pragma unroll
-                for (int v = 0; v < KP; ++v) out &= fmaf(nx, px[v], ny * py[v]) > h;
-                sep |= out;
-            }
+#pragma unroll 2
+            for (int e = 0; e < KP; ++e) sep |= beyond<KQ>(P->edge[e], qx, qy);
+            if (__all(sep)) return false;
+#pragma unroll 2
+            for (int e = 0; e < KQ; ++e) sep |= beyond<KP>(Q->edge[e], px, py);
             return !sep;
         } else {
             bool in_q[KQ], in_p[KP];
@@ -715,13 +722,13 @@ struct CheckGG : PrepNone {
             for (int v = 0; v < KP; ++v) in_p[v] = true;
 #pragma unroll 1
             for (int e = 0; e < KP; ++e) {
-                const float nx = P->nx[e], ny = P->ny[e], h = P->h[e];
+                const float nx = P->edge[e].nx, ny = P->edge[e].ny, h = P->edge[e].h;
 #pragma unroll
                 for (int v = 0; v < KQ; ++v) in_q[v] &= fmaf(nx, qx[v], ny * qy[v]) <= h;
             }
 #pragma unroll 1
             for (int e = 0; e < KQ; ++e) {
-                const float nx = Q->nx[e], ny = Q->ny[e], h = Q->h[e];
+                const float nx = Q->edge[e].nx, ny = Q->edge[e].ny, h = Q->edge[e].h;
 #pragma unroll
                 for (int v = 0; v < KP; ++v) in_p[v] &= fmaf(nx, px[v], ny * py[v]) <= h;
             }
@@ -735,27 +742,47 @@ struct CheckGG : PrepNone {
     }
 };
 
-// Convex polygon G (K vertices, padded) and circle (centre c, squared radius
-// rr): c in G's frame; a hit iff c is inside or its squared distance to some
-// edge segment is at most rr.
-template <int K>
-__device__ __forceinline__ bool poly_circle(const float4 P, const float2 c, const DPoly *G, float rr)
+// Convex polygon G (K vertices, padded) at N poses and M circles (squared
+// radius rr): a centre in G's frame; a hit iff it is inside or its squared
+// distance to some edge segment is at most rr. All N x M pairs go along one
+// walk over the edges, whose constants are read once for them.
+// (Scene 2 of those, where these pairs take the most time: 46 us with a walk for
+// each pair, 24 so.)
+template <int K, int N, int M>
+__device__ __forceinline__ void poly_circle(const float4 (&P)[N], const float2 (&c)[M], const DPoly *G, float rr,
+                                            bool (&hit)[N][M])
 {
-    const float dx = c.x - P.x;
-    const float dy = c.y - P.y;
-    const float lam = fmaf(dx, P.z, dy * P.w);
-    const float mu = fmaf(dy, P.z, -(dx * P.w));
-    bool inside = true;
-    float best = 3.0e38f;
-#pragma unroll 1
+    float lam[N][M], mu[N][M], best[N][M];
+    bool inside[N][M];
+#pragma unroll
+    for (int n = 0; n < N; ++n)
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+            const float dx = c[m].x - P[n].x;
+            const float dy = c[m].y - P[n].y;
+            lam[n][m] = fmaf(dx, P[n].z, dy * P[n].w);
+            mu[n][m] = fmaf(dy, P[n].z, -(dx * P[n].w));
+            inside[n][m] = true;
+            best[n][m] = 3.0e38f;
+        }
+#pragma unroll 2
     for (int e = 0; e < K; ++e) {
-        inside &= fmaf(G->nx[e], lam, G->ny[e] * mu) <= G->h[e];
-        const float ax = lam - G->vx[e], ay = mu - G->vy[e];
-        const float t = fminf(fmaxf(fmaf(ax, G->ex[e], ay * G->ey[e]) * G->il[e], 0.0f), 1.0f);
-        const float cx = fmaf(-t, G->ex[e], ax), cy = fmaf(-t, G->ey[e], ay);
-        best = fminf(best, fmaf(cx, cx, cy * cy));
+        const DEdge E = G->edge[e];
+#pragma unroll
+        for (int n = 0; n < N; ++n)
+#pragma unroll
+            for (int m = 0; m < M; ++m) {
+                inside[n][m] &= fmaf(E.nx, lam[n][m], E.ny * mu[n][m]) <= E.h;
+                const float ax = lam[n][m] - E.vx, ay = mu[n][m] - E.vy;
+                const float t = fminf(fmaxf(fmaf(ax, E.ex, ay * E.ey) * E.il, 0.0f), 1.0f);
+                const float cx = fmaf(-t, E.ex, ax), cy = fmaf(-t, E.ey, ay);
+                best[n][m] = fminf(best[n][m], fmaf(cx, cx, cy * cy));
+            }
     }
-    return inside | (best <= rr);
+#pragma unroll
+    for (int n = 0; n < N; ++n)
+#pragma unroll
+        for (int m = 0; m < M; ++m) hit[n][m] = inside[n][m] | (best[n][m] <= rr);
 }
 
 template <int K>
@@ -763,7 +790,6 @@ struct CheckGC : PrepNone {
     const DPoly *G;   // LDS
     float rr;
     __device__ __forceinline__ CheckGC(const DPoly *g, float r2) : G(g), rr(r2) {}
-    __device__ __forceinline__ bool operator()(const float4 P, const float2 Q) const { return poly_circle<K>(P, Q, G, rr); }
 };
 
 template <int K>
@@ -771,8 +797,45 @@ struct CheckCG : PrepNone {
     const DPoly *G;   // LDS
     float rr;
     __device__ __forceinline__ CheckCG(const DPoly *g, float r2) : G(g), rr(r2) {}
-    __device__ __forceinline__ bool operator()(const float2 P, const float4 Q) const { return poly_circle<K>(Q, P, G, rr); }
 };
+
+// The tests of an item at step t: found[r][s] = t where a[r] and b[s] overlap.
+template <int RI, int RJ, class PA, class PB, class Check>
+__device__ __forceinline__ void test_tile(const Check &chk, const PA (&a)[RI], const PB (&b)[RJ], int (&found)[RI][RJ],
+                                          int t)
+{
+#pragma unroll
+    for (int r = 0; r < RI; ++r)
+#pragma unroll
+        for (int s = 0; s < RJ; ++s)
+            if (chk(a[r], b[s])) found[r][s] = t;
+}
+
+template <int RI, int RJ, int K>
+__device__ __forceinline__ void test_tile(const CheckGC<K> &chk, const float4 (&a)[RI], const float2 (&b)[RJ],
+                                          int (&found)[RI][RJ], int t)
+{
+    bool hit[RI][RJ];
+    poly_circle<K>(a, b, chk.G, chk.rr, hit);
+#pragma unroll
+    for (int r = 0; r < RI; ++r)
+#pragma unroll
+        for (int s = 0; s < RJ; ++s)
+            if (hit[r][s]) found[r][s] = t;
+}
+
+template <int RI, int RJ, int K>
+__device__ __forceinline__ void test_tile(const CheckCG<K> &chk, const float2 (&a)[RI], const float4 (&b)[RJ],
+                                          int (&found)[RI][RJ], int t)
+{
+    bool hit[RJ][RI];
+    poly_circle<K>(b, a, chk.G, chk.rr, hit);
+#pragma unroll
+    for (int r = 0; r < RI; ++r)
+#pragma unroll
+        for (int s = 0; s < RJ; ++s)
+            if (hit[s][r]) found[r][s] = t;
+}
 
 // Raw buffer descriptor (CDNA: dword3 = 0x00020000) over `bytes` bytes.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t pose_rsrc(const char *base, uint32_t bytes)
@@ -916,11 +979,7 @@ __device__ __forceinline__ bool test_item(const DPair &pr, const char *__restric
         for (int r = 0; r < RI; ++r) a[r] = chk.prep_a(a[r]);
 #pragma unroll
         for (int s = 0; s < RJ; ++s) b[s] = chk.prep_b(b[s]);
-#pragma unroll
-        for (int r = 0; r < RI; ++r)
-#pragma unroll
-            for (int s = 0; s < RJ; ++s)
-                if (chk(a[r], b[s])) found[r][s] = t;
+        test_tile(chk, a, b, found, t);
     }
     bool any = false;
 #pragma unroll

@@ -36,11 +36,13 @@ constexpr int MAX_VERTICES = 8;
 // edge vectors (vertex e to e+1) with 1 / |edge|^2. k is 4 or 8: a polygon
 // of fewer vertices is padded with copies of vertex 0 and of edge 0, which
 // change none of the tests.
+struct alignas(16) DEdge {        // read as two 16-byte words
+    float nx, ny, h, il;          // normal and offset, 1 / |edge|^2
+    float vx, vy, ex, ey;         // first vertex, edge vector
+};
 struct DPoly {
     int32_t k, pad0, pad1, pad2;
-    float vx[MAX_VERTICES], vy[MAX_VERTICES];
-    float nx[MAX_VERTICES], ny[MAX_VERTICES], h[MAX_VERTICES];
-    float ex[MAX_VERTICES], ey[MAX_VERTICES], il[MAX_VERTICES];
+    DEdge edge[MAX_VERTICES];
 };
 
 // Reading of the conditional-probability approximation (mhc.h MHC_RISK_*).

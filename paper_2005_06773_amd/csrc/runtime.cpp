@@ -64,8 +64,8 @@ static double split_below_units_per_wave(int max_waves) { return max_waves < 102
 // blocks take fewer looks, smaller ones spread the pairs that meet over more
 // workgroups. Collision kernel on the 11-object scene: 13 us with half a block
 // a wave (sides of 32), 17 with one (16: a second round of looks); octagons,
-// whose tests take 30 times as long, 34 us with two blocks a wave, 47 with half
-// a block.
+// whose tests take 15 times as long, 39 us (mean of four scenes) with two blocks
+// a wave (sides of 16), 54 with eight (sides of 8).
 static double blocks_per_wave(int family) { return family == FAM_POLY ? 2.0 : 0.5; }
 
 // The strip height of traj_at for an n_u x n_w grid: a leaf's positions cover
@@ -502,8 +502,13 @@ static void build_layout_once(const mhc_scene *scenes, int n_scenes, int variant
         }
         if ((double)n_blocks >= blocks_per_wave(L.family) * max_waves) break;
     }
-    // large plans: several blocks to a look, whose row's boxes are read once
-    L.strip_len = max_waves > 0 ? (int)std::max<int64_t>(1, std::min<int64_t>(MAX_STRIP, n_blocks / max_waves)) : 1;
+    // Large plans: several blocks to a look, whose row's boxes are read once.
+    // Neighbouring blocks meet together, so a strip is long only where a wave
+    // still gets eight of them. Collision kernel with strips of three blocks
+    // and of one: octagons 43 and 32 us (mean of four scenes); with two and
+    // with four to eight a wave on the 64-scene batch: 380 and 338 us.
+    L.strip_len = max_waves > 0 ? (int)std::max<int64_t>(1, std::min<int64_t>(MAX_STRIP, n_blocks / (8 * (int64_t)max_waves)))
+                                : 1;
     int64_t n_strips = 0;
     L.strip0.clear();
     for (DPair &pr : L.pairs) {
@@ -582,29 +587,23 @@ static void fill_poly(const mhc_object &o, DPoly &g)
     g = DPoly{};
     g.k = padded_vertices(k);
     for (int e = 0; e < g.k; ++e) {
+        DEdge &d = g.edge[e];
         if (e >= k) {  // padding: copies of vertex 0 and of edge 0
-            g.vx[e] = g.vx[0];
-            g.vy[e] = g.vy[0];
-            g.nx[e] = g.nx[0];
-            g.ny[e] = g.ny[0];
-            g.h[e] = g.h[0];
-            g.ex[e] = g.ex[0];
-            g.ey[e] = g.ey[0];
-            g.il[e] = g.il[0];
+            d = g.edge[0];
             continue;
         }
         const int f = (e + 1) % k;
         const double ex = vx[f] - vx[e], ey = vy[f] - vy[e];
         const double len = std::hypot(ex, ey);
         const double nx = ey / len, ny = -ex / len;   // outward for a CCW polygon
-        g.vx[e] = (float)vx[e];
-        g.vy[e] = (float)vy[e];
-        g.nx[e] = (float)nx;
-        g.ny[e] = (float)ny;
-        g.h[e] = (float)(nx * vx[e] + ny * vy[e]);
-        g.ex[e] = (float)ex;
-        g.ey[e] = (float)ey;
-        g.il[e] = (float)(1.0 / (ex * ex + ey * ey));
+        d.vx = (float)vx[e];
+        d.vy = (float)vy[e];
+        d.nx = (float)nx;
+        d.ny = (float)ny;
+        d.h = (float)(nx * vx[e] + ny * vy[e]);
+        d.ex = (float)ex;
+        d.ey = (float)ey;
+        d.il = (float)(1.0 / (ex * ex + ey * ey));
     }
 }
 
