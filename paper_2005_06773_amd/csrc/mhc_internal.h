@@ -129,13 +129,21 @@ __host__ __device__ inline int strip_in_row(int row, int x, int grid)
 // grid (accelerations or speeds), column by column, the next strip backwards:
 // neighbouring positions are neighbours in both controls, so a leaf of them,
 // and a group of leaves, keeps close together over the horizon.
-__host__ __device__ inline int traj_at(int pos, int n_u, int n_w, int strip)
+__host__ __device__ inline void controls_at(int pos, int n_u, int n_w, int strip, int *k, int *l)
 {
     const int b = pos / (strip * n_w);
     const int k0 = b * strip, left = n_u - k0, rows = left < strip ? left : strip;
     const int r = pos - k0 * n_w;
     const int c = r / rows;
-    return (k0 + (r - c * rows)) * n_w + ((b & 1) ? n_w - 1 - c : c);
+    *k = k0 + (r - c * rows);
+    *l = (b & 1) ? n_w - 1 - c : c;
+}
+
+__host__ __device__ inline int traj_at(int pos, int n_u, int n_w, int strip)
+{
+    int k, l;
+    controls_at(pos, n_u, n_w, strip, &k, &l);
+    return k * n_w + l;
 }
 
 constexpr int WG = 256;           // threads per workgroup, other kernels
