@@ -506,15 +506,13 @@ __global__ __launch_bounds__(K1_WG) void k1_trajgen(const DObj *__restrict__ obj
 // ===========================================================================
 // K2: collision recognition (Sec. IV-C).
 //
-// Every trajectory pair of every object pair is decided at every step. A wave
-// takes a unit: item rows by item columns of one object pair, an
-// item being an RI x RJ micro-tile of trajectory pairs (of neighbouring
-// positions). It first forms, lane l for step l, the boxes of the unit's two
-// groups of trajectories from their leaves' boxes; at a step where the boxes
-// lie further apart than the two shapes reach, no pair of the unit overlaps.
-// The steps left over are walked from the last to the first, each lane testing
-// its micro-tile and recording the step of each overlap, so the value left at
-// the end is the earliest colliding step (or -1). Tests are exact closed-shape
+// Every trajectory pair of every object pair is decided at every step, most of
+// them together: at a step at which the boxes of two leaves of trajectories lie
+// apart, no pair of theirs overlaps. What is left is tested in units, item rows
+// by item columns of one object pair, an item being an RI x RJ micro-tile of
+// trajectory pairs (of neighbouring positions); the steps of an item go from
+// later to earlier, and the earliest overlap of a pair is kept in LDS. Tests are
+// exact closed-shape
 // tests in FP32:
 //   rectangle-rectangle: separating axes u_P, v_P, u_Q, v_Q; the projected
 //     half extents use |cos(psi_Q - psi_P)| and |sin(psi_Q - psi_P)|;
