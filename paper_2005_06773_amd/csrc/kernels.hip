@@ -864,14 +864,25 @@ __device__ __forceinline__ float2 load_pose<float2>(__amdgpu_buffer_rsrc_t r, ui
 // at that step, along x or along y, by more than the rounding of the tests.
 //
 // That no test of such a step finds an overlap holds for the FP32 tests as
-// they are computed, not only for the shapes: two shapes whose bounds lie m
-// apart are separated by at least 0.38 m along one of the edge normals the
-// tests use (neighbouring edge normals of a Minkowski sum of outlines with
-// interior angles of at least 45 degrees turn by at most 135 degrees;
-// rectangles: 0.7 m), the boxes' and the tests' projections are off by less
-// than 64 half-ulps of the largest coordinate, and m is 256 of them
-// (kBoxSlack). Boxes with an infinite side separate nothing, and the
-// comparison is made so that a NaN keeps the step.
+// they are computed, not only for the shapes. With u = 2^-24 and M the largest
+// coordinate of the two boxes, positions are at most M, half extents 1.42 M and
+// vertices 2 M, so that the roundings add up to at most about
+//   rectangles  45 u M: projections onto the other's axes 25, radii 15, axes 5;
+//   outlines    60 u M: a vertex in the other's frame 25 a coordinate, an edge's
+//                       normal, product and offset 20, axes 5;
+//   circles     55 u M: centre in the frame 8 a coordinate, nearest point of an
+//                       edge 25 a coordinate, square and radius 7, axes 5;
+//   boxes        8 u M: extents, sides and the gap itself.
+// Shapes whose boxes lie m apart are separated by at least 0.7 m along one of
+// the axes of a rectangle test, by 0.38 m along one of the edge normals of an
+// outline test (neighbouring normals turn by at most 135 degrees, interior
+// angles being 45 degrees or more; the cosine of half of it), and a circle by m
+// itself. A step is left out at m > 256 u M (kBoxSlack): 98 u M against 68.
+// kBoxLeast keeps that from underflow: the tests' squares are 0 in FP32 below
+// 1e-22 m and the circle tests then find overlaps that are none, but a gap of
+// 2^-50 m leaves at least 2^-100 between the squares that they compare.
+// Boxes with an infinite side separate nothing, and the comparison is made so
+// that a NaN keeps the step.
 __device__ __forceinline__ float box_size(const float4 a)
 {
     return fmaxf(fmaxf(fabsf(a.x), fabsf(a.y)), fmaxf(fabsf(a.z), fabsf(a.w)));
@@ -881,7 +892,7 @@ __device__ __forceinline__ float box_size(const float4 a)
 __device__ __forceinline__ bool boxes_meet(const float4 a, const float4 b, float size)
 {
     const float gx = fmaxf(b.x - a.y, a.x - b.y), gy = fmaxf(b.z - a.w, a.z - b.w);
-    return !(fmaxf(gx, gy) > size * kBoxSlack);
+    return !(fmaxf(gx, gy) > fmaf(size, kBoxSlack, kBoxLeast));
 }
 
 // The boxes at this lane's step t of `side` leaves from leaf0 on (past those and
