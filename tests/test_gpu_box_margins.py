@@ -70,3 +70,75 @@ def test_scenes_so_small_that_squares_underflow(mhc, ctx, scale, outline):
     if outline:
         s.objects[1].outline = np.array([[math.cos(a), math.sin(a)] for a in np.arange(6) * math.pi / 3]) * 0.2 * scale
     same_as_testing_every_step(mhc, ctx, s, f"scale {scale} outline {outline}")
+
+
+def _sharp(angle_deg, reach):
+    """A triangle with one corner of angle_deg, `reach` ahead of the tracked
+    position, the sharpest that is accepted at 45 degrees."""
+    half = math.radians(angle_deg) / 2.0
+    h = 1.5 * reach * math.tan(half)
+    return np.array([[reach, 0.0], [-0.5 * reach, h], [-0.5 * reach, -h]])
+
+
+def _corners(o):
+    if o.kind != sg.VEHICLE:
+        return None
+    v = o.outline
+    if v is None:
+        l, w = o.length / 2.0, o.width / 2.0
+        v = np.array([[l, -w], [l, w], [-l, w], [-l, -w]])
+    return v
+
+
+def _half_extent(o, axis):
+    """Half of what the object's box covers along an axis (its shape's bounds
+    about the tracked position, turned by its heading)."""
+    if o.kind != sg.VEHICLE:
+        return o.radius
+    v = np.abs(_corners(o)).max(axis=0)
+    c, s = abs(math.cos(o.heading)), abs(math.sin(o.heading))
+    return v[0] * c + v[1] * s if axis == 0 else v[0] * s + v[1] * c
+
+
+def _near_touch_scene(seed, shift, overlap, sharp):
+    """An EGO at (shift, shift) from the scene's origin and shapes all around
+    it whose boxes stop 0 to 3 thresholds of the margin away from its box,
+    corner towards corner where they have sharp ones."""
+    rng = np.random.default_rng(seed)
+    ego = _still(sg.VEHICLE, 0.0, 0.0, float(rng.uniform(-math.pi, math.pi)), 1.0, n=2)
+    if sharp:
+        ego.outline = _sharp(45.5, 2.0)
+    objs = [ego]
+    margin = 2.0 ** -16 * max(abs(shift), 4.0)
+    for k in range(36):
+        d = float(rng.choice([0.0, math.pi / 2, math.pi, -math.pi / 2]))     # where it lies
+        kind = sg.VEHICLE if overlap == sg.OVERLAP_PIP or k % 3 else sg.PEDESTRIAN
+        face = d + math.pi + (float(rng.normal(0.0, 0.02)) if k % 2 else float(rng.uniform(-math.pi, math.pi)))
+        o = _still(kind, 0.0, 0.0, face, 0.4 + 0.1 * (k % 5), n=1 + k % 9)
+        if kind == sg.VEHICLE and sharp and k % 4:
+            o.outline = _sharp(45.2 + k % 3 * 20, 1.0 + 0.5 * (k % 4))
+        axis = 0 if abs(math.cos(d)) > 0.5 else 1
+        dist = _half_extent(ego, axis) + _half_extent(o, axis) + float(rng.uniform(-0.2, 3.0)) * margin
+        side = float(rng.normal(0.0, 0.3))
+        o.x = math.cos(d) * dist if axis == 0 else side
+        o.y = math.sin(d) * dist if axis == 1 else side
+        objs.append(o)
+    ego.heading = 0.0 if seed % 2 and sharp else ego.heading
+    if shift:
+        objs.append(_still(sg.VEHICLE, -2.0 * shift, -2.0 * shift, 0.0, 1.0, n=1))   # puts the origin in between
+    return sg.Scene(objs, 2, 0.1, pairs=sg.PAIRS_EGO, overlap=overlap)
+
+
+@pytest.mark.parametrize("overlap", [sg.OVERLAP_EXACT, sg.OVERLAP_PIP])
+@pytest.mark.parametrize("sharp", [False, True])
+@pytest.mark.parametrize("shift", [0.0, 3.0e4, 1.0e9])
+def test_turned_shapes_at_the_margin(mhc, ctx, shift, sharp, overlap):
+    """Turned rectangles, circles and outlines whose sharpest corners are just
+    above 45 degrees, in both overlap modes, where the margin decides; far out
+    it is wider than the shapes, and their poses are as coarse as the margin."""
+    hits = 0
+    for seed in range(8):
+        s = _near_touch_scene(seed, shift, overlap, sharp)
+        got = same_as_testing_every_step(mhc, ctx, s, f"seed {seed} shift {shift} sharp {sharp} overlap {overlap}")
+        hits += int((got["first_hit"] >= 0).sum())
+    print(f"{hits} colliding pairs", flush=True)
