@@ -1593,7 +1593,11 @@ extern "C" mhc_status mhc_plan_execute_stages(mhc_plan *pl, const mhc_result *de
     HIPC(hipSetDevice(ctx->device));
     const hipStream_t s = static_cast<hipStream_t>(hip_stream);
     Launch X = make_launch(pl->L, pl->dbuf, dev_out, true, ctx->n_cu);
-    if (stages & MHC_STAGE_TRAJ) HIPC(launch_trajgen(X, s));
+    // The first hits are the collision stage's: the trajectory kernel clears
+    // them only where that stage follows in this call, else it does so itself.
+    Launch traj = X;
+    if (!(stages & MHC_STAGE_COLLIDE)) traj.hits = nullptr;
+    if (stages & MHC_STAGE_TRAJ) HIPC(launch_trajgen(traj, s));
     X.clear_hits = !(stages & MHC_STAGE_TRAJ);
     if (stages & MHC_STAGE_COLLIDE) HIPC(launch_collide(X, s));
     if (stages & MHC_STAGE_RISK) HIPC(launch_risk(X, s));
