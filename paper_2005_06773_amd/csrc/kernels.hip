@@ -1242,12 +1242,12 @@ __device__ __forceinline__ void block_tables(K2Lds &w, int slot, const DPair &pr
 // launch is bound by the latency of its dependent reads (pair, boxes, poses,
 // tables: 1 to 2 us each when first touched on a CU), so each of them is made
 // once per block, by waves side by side.
-// A launch may run one part of the plan: rounds [round0, round1). The plan's
-// strips fill full_rows rows and last_row strips of the next.
+// A launch may run a part of the plan (strips_before_part): its strips, from
+// strip_lo on, fill full_rows rows and last_row strips of the next.
 template <int V, int FAM, bool TL>
 __global__ __launch_bounds__(K2_WG) __attribute__((amdgpu_waves_per_eu(kCollideMinWaves<FAM>))) void k2_collide(
     const DPair *__restrict__ pairs, const DObj *__restrict__ objs, const int64_t *__restrict__ strip0, int n_pairs,
-    int full_rows, int last_row, int strip_len, int side_shift, int round0, int round1, const char *__restrict__ poses,
+    int64_t strip_lo, int full_rows, int last_row, int strip_len, int side_shift, const char *__restrict__ poses,
     int16_t *__restrict__ hits, const unsigned long long *__restrict__ pfix, unsigned long long *__restrict__ qacc,
     unsigned long long *__restrict__ hist, const DPoly *__restrict__ polys)
 {
@@ -1273,10 +1273,10 @@ __global__ __launch_bounds__(K2_WG) __attribute__((amdgpu_waves_per_eu(kCollideM
     workgroup_sync();
     auto next = [](int at) { return at == 2 ? 0 : at + 1; };
     int alive_at = 0, units_at = 0;
-    for (int r = round0; r < round1; ++r) {
-        const int row = r * NW + wave, x = strip_in_row(row, (int)blockIdx.x, (int)gridDim.x);
+    for (int row0 = 0; row0 < full_rows + (last_row > 0); row0 += NW) {
+        const int row = row0 + wave, x = strip_in_row(row, (int)blockIdx.x, (int)gridDim.x);
         if (row < full_rows || (row == full_rows && x < last_row)) {
-            const int64_t g = (int64_t)row * gridDim.x + x;
+            const int64_t g = strip_lo + (int64_t)row * gridDim.x + x;
             const int p = pair_of_strip(strip0, n_pairs, g);
             const DPair &pr = pairs[p];
             int bi, bj;
@@ -1830,22 +1830,18 @@ static hipError_t launch_clear_hits(const Launch &L, hipStream_t s)
 template <int V, int FAM, bool TL>
 static hipError_t launch_k2(const Launch &L, hipStream_t s)
 {
-    const int parts = L.collide_parts > 1 ? L.collide_parts : 1;
-    const int first = L.collide_only > 0 ? L.collide_only - 1 : 0;
-    const int last = L.collide_only > 0 ? L.collide_only : parts;
-    if (first >= parts) return hipErrorInvalidValue;
-    const int64_t per_round = (int64_t)L.k2_grid * (K2_WG / WAVE);
-    const int64_t rounds = (L.n_strips + per_round - 1) / per_round;
-    if (rounds * (K2_WG / WAVE) >= INT_MAX) return hipErrorInvalidValue;
-    for (int part = first; part < last; ++part) {
-        hipLaunchKernelGGL((k2_collide<V, FAM, TL>), dim3(L.k2_grid), dim3(K2_WG), 0, s, L.pairs, L.objs, L.strip0, L.n_pairs,
-                           (int)(L.n_strips / L.k2_grid), (int)(L.n_strips % L.k2_grid), L.strip_len, L.side_shift,
-                           (int)(rounds * part / parts), (int)(rounds * (part + 1) / parts), L.poses, L.hits, L.pfix,
-                           L.qacc, L.hist, L.polys);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
+    int64_t lo = 0, hi = L.n_strips;
+    if (L.collide_parts > 0) {
+        if (L.part_lo < 0 || L.part_hi > L.collide_parts || L.part_lo > L.part_hi) return hipErrorInvalidValue;
+        lo = strips_before_part(L.n_strips, L.part_lo, L.collide_parts);
+        hi = strips_before_part(L.n_strips, L.part_hi, L.collide_parts);
     }
-    return hipSuccess;
+    if (lo == hi) return hipSuccess;
+    if (L.n_strips / L.k2_grid >= INT_MAX - K2_WG) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k2_collide<V, FAM, TL>), dim3(L.k2_grid), dim3(K2_WG), 0, s, L.pairs, L.objs, L.strip0, L.n_pairs,
+                       lo, (int)((hi - lo) / L.k2_grid), (int)((hi - lo) % L.k2_grid), L.strip_len, L.side_shift,
+                       L.poses, L.hits, L.pfix, L.qacc, L.hist, L.polys);
+    return hipGetLastError();
 }
 
 template <int V, int FAM, bool TL>

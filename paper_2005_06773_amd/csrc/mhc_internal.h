@@ -115,6 +115,10 @@ __host__ __device__ inline void strip_at(const DPair &pr, uint32_t u, int *bi, i
     *sj = (int)((q + ru * (uint32_t)pr.step_j) % (uint32_t)pr.nsj);
 }
 
+// A plan of n strips cut into `parts`: the strips before part `part`. No part is
+// empty while there are as many strips.
+inline int64_t strips_before_part(int64_t n, int part, int parts) { return n / parts * part + n % parts * part / parts; }
+
 // The strip of its row of `grid` strips that workgroup x looks at: the
 // workgroups are turned from row to row, so that none meets the same part of
 // every pair.
@@ -246,8 +250,8 @@ struct Launch {
     double *att_w;                // attribution [b][i] per object
     double *ct_w;                 // criticality over time [s][i] per object
     double *crit_t, *traj_crit_t, *attrib, *traj_attrib;
-    int collide_parts;            // the collision plan runs as this many launches (0 or 1: one)
-    int collide_only;             // 0: launch every part; k > 0: launch only part k - 1
+    int collide_parts;            // parts of the collision plan (0: launch all of it)
+    int part_lo, part_hi;         // of them, those that one launch takes together
     int clear_hits;               // collide writes -1 over the first hits first (no trajgen in this call does)
     int one_track;                // some object follows the one-track model (heavier trajectory kernel)
     int variant;

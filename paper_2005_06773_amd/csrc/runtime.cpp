@@ -769,6 +769,12 @@ Launch make_launch(const Layout &L, char *base, const mhc_result *dev_out, bool 
     return X;
 }
 
+int collide_parts(const Layout &L, int64_t checks_per_part)
+{
+    const int64_t want = (L.n_checks + checks_per_part - 1) / checks_per_part;
+    return (int)std::max<int64_t>(2, std::min<int64_t>({want, L.strip0.back(), 64}));
+}
+
 hipError_t launch_all(const Launch &X, hipStream_t s)
 {
     hipError_t e = launch_trajgen(X, s);
@@ -885,7 +891,7 @@ extern "C" mhc_status mhc_query_sizes(const mhc_scene *scene, mhc_sizes *out)
     return MHC_OK;
 }
 
-// Walks a collision plan the way k2_collide decodes it: rounds -> workgroups ->
+// Walks a collision plan the way k2_collide decodes it: launches -> workgroups ->
 // waves -> strips -> blocks -> units -> lanes -> items -> trajectory pairs, counting how
 // often each item is tested and every index that leaves its pair.
 static void walk_plan(const Layout &L, mhc_plan_info &info)
@@ -929,51 +935,57 @@ static void walk_plan(const Layout &L, mhc_plan_info &info)
     const int64_t n_strips = bad ? 0 : L.strip0.back();
     const int64_t per_round = (int64_t)L.k2_grid * (K2_WG / WAVE);
     const int64_t rounds = (n_strips + per_round - 1) / std::max<int64_t>(1, per_round);
-    for (int64_t rw = 0; rw < rounds * (K2_WG / WAVE) && !bad; ++rw)
-        for (int wg = 0; wg < L.k2_grid; ++wg) {
-            const int64_t g = rw * L.k2_grid + strip_in_row((int)rw, wg, L.k2_grid);
-            if (g >= n_strips) continue;
-            const size_t p = (size_t)(std::upper_bound(L.strip0.begin(), L.strip0.end(), g) - L.strip0.begin()) - 1;
-            const DPair &pr = L.pairs[p];
-            const TileShape ts = kTiles[L.variant][pr.cls];
-            const DObj &oa = L.objs[pr.a], &ob = L.objs[pr.b];
-            const int ri = ts.ri, rj = ts.rj, per = WAVE >> pr.tshift;
-            int bi, sj;
-            strip_at(pr, (uint32_t)(g - L.strip0[p]), &bi, &sj);
-            if (bi < 0 || bi >= pr.nbi || sj < 0 || sj >= pr.nsj) ++bad;
-            const int units_of = pr.block_ur << pr.block_ucs;
-            for (int x = 0; x < units_of * L.strip_len; ++x) {
-                const int bj = sj * L.strip_len + x / units_of, u = x % units_of;
-                if (bj >= pr.nbj) break;
-                const int ui = bi * pr.block_ur + (u >> pr.block_ucs);
-                const int uj = (bj << pr.block_ucs) + (u & ((1 << pr.block_ucs) - 1));
-                if (ui >= pr.nui || uj >= pr.nuj) continue;
-                ++units;
-                for (int lane = 0; lane < per; ++lane) {   // the lanes of part 0
-                    const int ig = ui * (per >> pr.bshift) + (lane >> pr.bshift);
-                    const int jg = (uj << pr.bshift) + (lane & ((1 << pr.bshift) - 1));
-                    if (ig >= pr.n_ig || jg >= pr.n_jg) continue;
-                    if (ig < 0 || jg < 0) {
-                        ++bad;
-                        continue;
-                    }
-                    for (int r = 0; r < ri; ++r)
-                        for (int sidx = 0; sidx < rj; ++sidx) {
-                            const int64_t pi = (int64_t)ig * ri + r, pj = (int64_t)jg * rj + sidx;
-                            if (pi >= pr.Ta || pj >= pr.Tb) continue;  // idle tile slot
-                            const int64_t i = traj_at((int)pi, oa.n_u, oa.n_w, oa.strip);
-                            const int64_t j = traj_at((int)pj, ob.n_u, ob.n_w, ob.strip);
-                            const int64_t h = pr.hit_off + i * pr.Tb + j;
-                            if (h < 0 || h >= L.n_hits) ++bad;
-                            if (oa.q_row + i * oa.n_scene_obj + ob.local >= L.n_q ||
-                                ob.q_row + j * ob.n_scene_obj + oa.local >= L.n_q)
-                                ++bad;
+    // cut as a large server tick cuts it: every strip in one of the parts
+    const int parts = collide_parts(L, kPartChecks);
+    for (int part = 0; part < parts && !bad; ++part) {
+        const int64_t lo = strips_before_part(n_strips, part, parts), hi = strips_before_part(n_strips, part + 1, parts);
+        if (lo < 0 || hi > n_strips || (lo >= hi && n_strips >= 2)) ++bad;
+        for (int64_t rw = 0; rw * L.k2_grid < hi - lo; ++rw)
+            for (int wg = 0; wg < L.k2_grid; ++wg) {
+                const int64_t g = lo + rw * L.k2_grid + strip_in_row((int)rw, wg, L.k2_grid);
+                if (g >= hi) continue;
+                const size_t p = (size_t)(std::upper_bound(L.strip0.begin(), L.strip0.end(), g) - L.strip0.begin()) - 1;
+                const DPair &pr = L.pairs[p];
+                const TileShape ts = kTiles[L.variant][pr.cls];
+                const DObj &oa = L.objs[pr.a], &ob = L.objs[pr.b];
+                const int ri = ts.ri, rj = ts.rj, per = WAVE >> pr.tshift;
+                int bi, sj;
+                strip_at(pr, (uint32_t)(g - L.strip0[p]), &bi, &sj);
+                if (bi < 0 || bi >= pr.nbi || sj < 0 || sj >= pr.nsj) ++bad;
+                const int units_of = pr.block_ur << pr.block_ucs;
+                for (int x = 0; x < units_of * L.strip_len; ++x) {
+                    const int bj = sj * L.strip_len + x / units_of, u = x % units_of;
+                    if (bj >= pr.nbj) break;
+                    const int ui = bi * pr.block_ur + (u >> pr.block_ucs);
+                    const int uj = (bj << pr.block_ucs) + (u & ((1 << pr.block_ucs) - 1));
+                    if (ui >= pr.nui || uj >= pr.nuj) continue;
+                    ++units;
+                    for (int lane = 0; lane < per; ++lane) {   // the lanes of part 0
+                        const int ig = ui * (per >> pr.bshift) + (lane >> pr.bshift);
+                        const int jg = (uj << pr.bshift) + (lane & ((1 << pr.bshift) - 1));
+                        if (ig >= pr.n_ig || jg >= pr.n_jg) continue;
+                        if (ig < 0 || jg < 0) {
+                            ++bad;
+                            continue;
                         }
-                    uint8_t &s = seen[(size_t)(item_base[p] + (int64_t)ig * pr.n_jg + jg)];
-                    if (s < 255) ++s;
+                        for (int r = 0; r < ri; ++r)
+                            for (int sidx = 0; sidx < rj; ++sidx) {
+                                const int64_t pi = (int64_t)ig * ri + r, pj = (int64_t)jg * rj + sidx;
+                                if (pi >= pr.Ta || pj >= pr.Tb) continue;  // idle tile slot
+                                const int64_t i = traj_at((int)pi, oa.n_u, oa.n_w, oa.strip);
+                                const int64_t j = traj_at((int)pj, ob.n_u, ob.n_w, ob.strip);
+                                const int64_t h = pr.hit_off + i * pr.Tb + j;
+                                if (h < 0 || h >= L.n_hits) ++bad;
+                                if (oa.q_row + i * oa.n_scene_obj + ob.local >= L.n_q ||
+                                    ob.q_row + j * ob.n_scene_obj + oa.local >= L.n_q)
+                                    ++bad;
+                            }
+                        uint8_t &s = seen[(size_t)(item_base[p] + (int64_t)ig * pr.n_jg + jg)];
+                        if (s < 255) ++s;
+                    }
                 }
             }
-        }
+    }
     int64_t uncovered = 0, repeated = 0;
     for (uint8_t c : seen) {
         uncovered += c == 0;

@@ -19,9 +19,9 @@
 // that one slot always stays open to the other frames; those may then go
 // ahead of a large frame that waits for a slot. Frames of either kind keep
 // their arrival order among themselves. On the GPU such a tick's collision
-// plan runs as several launches of at most about min(max_checks_per_tick,
-// 1e9) checks each, planned for 4/5 of the resident waves and enqueued one
-// ahead of the GPU as the earlier ones end, so that the other slots' kernels
+// plan runs as several launches of at most about max_checks_per_tick checks
+// and about 0.4 ms each, planned for 4/5 of the resident waves and enqueued
+// one ahead of the GPU as the earlier ones end, so that the other slots' kernels
 // find room on every CU beside it and between its launches, also where the
 // slots' streams share a hardware queue.
 #include <algorithm>
@@ -106,24 +106,22 @@ public:
     virtual void shutdown() {}
 };
 
-// Checks per collision launch of a large tick, at most (about 0.4 ms of the
-// GPU): a tick of another slot that shares the large tick's hardware queue
-// waits for at most two such launches.
-constexpr int64_t kPartChecks = 1000000000;
-
 // One slot of the GPU executor.
 struct TickSlot {
     hipStream_t stream = nullptr;
     hipEvent_t done = nullptr;          // the tick's results are in pinned memory
     hipEvent_t kernels_done = nullptr;  // a large tick's kernels have ended
     bool copies_pending = false;        // a large tick's result copies are not yet enqueued
-    // A large tick's collision parts are enqueued one ahead of the GPU (part
-    // k once part k - 2 has ended, part_ev[k % 2]), so that a tick of another
-    // slot whose stream shares this one's hardware queue waits for at most
-    // two parts, not for the whole frame.
+    // A large tick's collision plan is cut into parts (of at most kPartChecks)
+    // and launched `group` parts at a time, one launch ahead of the GPU (launch
+    // k once launch k - 2 has ended, part_ev[k % 2]), so that a tick of another
+    // slot whose stream shares this one's hardware queue waits for at most two
+    // launches, not for the whole frame.
     hipEvent_t part_ev[2] = {nullptr, nullptr};
     Launch X{};                         // the large tick's launch
     int next_part = 0, parts = 0;
+    int launches = 0, group = 1, max_group = 1;
+    int64_t ended_ns = 0;               // when the last launch that has ended was seen to
     char *dbuf = nullptr;
     size_t dbytes = 0;
     char *pin_in = nullptr;
@@ -143,6 +141,21 @@ struct TickSlot {
 // Pinned staging per slot and direction from the start: a tick of small
 // frames (tens of scenes of the batched size mix) fits without growing it.
 constexpr size_t kInitialStaging = (size_t)4 << 20;
+
+// Parts that a large tick's next launch takes together, after launches of
+// `group` parts ended `took_ns` apart: about 0.4 ms of the GPU. How long a part
+// takes depends on what meets in it, so the launches start at one part and
+// double while two of their length would fit, up to max_group (as many checks
+// as a tick of small frames may hold). 40-object frame (4.1e10 checks) from
+// submission to its results: 2.3 ms with a launch a part, 41 of 18 us each with
+// 40 us from a launch's end to the start of the next but one; 1.2 ms so. Small
+// frames beside it 0.16 to 0.17 ms at the 99th percentile either way.
+constexpr int64_t kLaunchNs = 400 * 1000;
+int next_group(int group, int64_t took_ns, int max_group)
+{
+    if (took_ns > kLaunchNs) return std::max(1, (int)(group * kLaunchNs / took_ns));
+    return 2 * took_ns <= kLaunchNs ? std::min(max_group, 2 * group) : group;
+}
 
 // Grows a pinned staging buffer to hold `want` bytes, at least doubling it,
 // so that a slot's buffers are replaced a logarithmic number of times and
@@ -182,15 +195,16 @@ public:
         return waves[v][fam][tl];
     }
 
-    // Enqueues the next collision part of a large tick; after the last, the
+    // Enqueues the next collision parts of a large tick; after the last, the
     // risk stage and the event its result copies wait for.
-    static hipError_t enqueue_part(TickSlot &t)
+    static hipError_t enqueue_parts(TickSlot &t)
     {
         Launch X = t.X;
-        X.collide_only = t.next_part + 1;
+        X.part_lo = t.next_part;
+        X.part_hi = t.next_part = std::min(t.parts, t.next_part + t.group);
         hipError_t e = launch_collide(X, t.stream);
-        if (e == hipSuccess) e = hipEventRecord(t.part_ev[t.next_part % 2], t.stream);
-        ++t.next_part;
+        if (e == hipSuccess) e = hipEventRecord(t.part_ev[t.launches % 2], t.stream);
+        ++t.launches;
         if (e == hipSuccess && t.next_part == t.parts) {
             e = launch_risk(X, t.stream);
             if (e == hipSuccess) e = hipEventRecord(t.kernels_done, t.stream);
@@ -237,7 +251,7 @@ public:
         }
         Launch X = make_launch(t.L, t.dbuf, nullptr, keep_hits, n_cu);
         // A tick above the check cap (one large frame) runs its collision
-        // plan as launches of at most about that many checks each, enqueued
+        // plan as launches of at most about that many checks, enqueued
         // one ahead of the GPU as the earlier ones end (poll), so that the
         // other slots' ticks get the GPU in between even where their streams
         // share this one's hardware queue. Its result copies are enqueued
@@ -246,13 +260,16 @@ public:
         // result copies of the other slots' ticks would wait behind it.
         t.copies_pending = large;
         if (large) {
-            const int64_t per_part = std::min<int64_t>(max_checks_per_tick, kPartChecks);
-            X.collide_parts = (int)std::max<int64_t>(2, std::min<int64_t>(64, (t.L.n_checks + per_part - 1) / per_part));
+            const int64_t part_checks = std::min(max_checks_per_tick, kPartChecks);
+            X.collide_parts = collide_parts(t.L, part_checks);
+            t.max_group = (int)std::min<int64_t>(max_checks_per_tick / part_checks, X.collide_parts);
             t.X = X;
             t.parts = X.collide_parts;
-            t.next_part = 0;
+            t.next_part = t.launches = 0;
+            t.group = 1;
+            t.ended_ns = 0;
             if (e == hipSuccess) e = launch_trajgen(X, t.stream);
-            while (e == hipSuccess && t.next_part < 2) e = enqueue_part(t);
+            while (e == hipSuccess && t.launches < 2) e = enqueue_parts(t);
         } else {
             if (e == hipSuccess) e = launch_all(X, t.stream);
             if (e == hipSuccess) e = enqueue_results(t.results, t.L, n, t.dbuf, t.pin_out, t.dsts.data(), t.stream);
@@ -269,9 +286,13 @@ public:
     {
         TickSlot &t = slots[slot];
         while (t.copies_pending && t.next_part < t.parts) {
-            const hipError_t k = hipEventQuery(t.part_ev[t.next_part % 2]);  // part next_part - 2
+            const hipError_t k = hipEventQuery(t.part_ev[t.launches % 2]);  // launch `launches` - 2
             if (k == hipErrorNotReady) return 0;
-            const hipError_t e = k == hipSuccess ? enqueue_part(t) : k;
+            // from one launch's end to the next's: what a group takes
+            const int64_t now = now_ns();
+            if (t.ended_ns) t.group = next_group(t.group, now - t.ended_ns, t.max_group);
+            t.ended_ns = now;
+            const hipError_t e = k == hipSuccess ? enqueue_parts(t) : k;
             if (e != hipSuccess) {
                 err = std::string("tick failed: ") + hipGetErrorString(e);
                 return -1;
