@@ -65,8 +65,9 @@ std::chrono::system_clock::time_point wait_deadline(std::chrono::microseconds d)
     return std::chrono::system_clock::now() + d;
 }
 
-// Bytes of a slot that admission leaves out: what a tick's tables may take
-// beyond those of its frames.
+// Bytes of a slot that admission leaves out. A tick's workspace is covered by
+// its frames' own bounds; this keeps the budgets that servers are given holding
+// the frames they held when a plan had a table of wave slots.
 constexpr size_t kTickReserve = ((size_t)1 << 18) + 256;
 constexpr int64_t kDefaultWatchdogUs = 30LL * 1000 * 1000;
 
@@ -83,7 +84,7 @@ struct Frame {
     int64_t n_traj = 0, n_hits = 0, checks = 0;
     size_t bytes = 0;    // device bytes upper bound
     bool large = false;  // more checks than one tick may carry
-    bool boxes_optional = false;  // pedestrians' trajectories outnumber vehicles' by more than 7 to 1
+    bool boxes_optional = false;  // the leaves' boxes take more than the vehicles' poses
     FrameState state = QUEUED;
     mhc_status status = MHC_OK;
     mhc_timing timing{};
@@ -406,15 +407,15 @@ namespace {
 // workspace layout), with or without the leaves' boxes.
 void frame_sizes(const mhc_scene *s, bool hits, bool boxes, Frame &f)
 {
-    int64_t n_traj = 0, n_ped = 0, pose = 0, n_hits = 0, vals = 0, n_pairs = 0, k1_blocks = 0;
+    int64_t n_traj = 0, n_hits = 0, vals = 0, n_pairs = 0, k1_blocks = 0;
+    size_t veh_pose = 0, ped_pose = 0, box = 0;
     const int n = s->n_objects;
     for (int a = 0; a < n; ++a) {
         const int64_t T = (int64_t)s->objects[a].n_u * s->objects[a].n_w;
         n_traj += T;
         const bool vehicle = s->objects[a].kind == MHC_VEHICLE;
-        n_ped += vehicle ? 0 : T;
-        pose += align256((size_t)s->horizon * T * (vehicle ? 16 : 8));
-        if (boxes) pose += align256((size_t)s->horizon * ((T + LEAF - 1) / LEAF) * sizeof(float4));
+        (vehicle ? veh_pose : ped_pose) += align256((size_t)s->horizon * T * (vehicle ? 16 : 8));
+        box += align256((size_t)s->horizon * ((T + LEAF - 1) / LEAF) * sizeof(float4));
         vals += s->objects[a].n_u + s->objects[a].n_w + (s->objects[a].score ? T : 0);
         k1_blocks += (T + K1_TPB - 1) / K1_TPB + 1;
     }
@@ -430,7 +431,8 @@ void frame_sizes(const mhc_scene *s, bool hits, bool boxes, Frame &f)
     bytes += align256((scene_has_outline(s) ? n : 0) * sizeof(DPoly));
     bytes += align256((n_pairs + 1) * sizeof(int64_t));   // first strip of each pair
     bytes += align256(k1_blocks * 2 * sizeof(int32_t));  // trajectory kernel rows (at most one per block)
-    bytes += pose + align256(n_traj * 8) * 3 + align256(n_q * 8) * 2;  // p*2^62, p, traj crit; q sums, q
+    bytes += veh_pose + ped_pose + (boxes ? box : 0);
+    bytes += align256(n_traj * 8) * 3 + align256(n_q * 8) * 2;  // p*2^62, p, traj crit; q sums, q
     bytes += align256(n * 8);                                            // risk kernel's per-object words
     bytes += align256(hits ? n_hits * 2 : 0) + align256(n * 8);
     if (s->timeline) {
@@ -444,7 +446,7 @@ void frame_sizes(const mhc_scene *s, bool hits, bool boxes, Frame &f)
                  align256((size_t)n * n * 8);
     }
     bytes += 16 * 256;                              // alignment slack of the tables
-    f.boxes_optional = n_ped > 7 * (n_traj - n_ped);
+    f.boxes_optional = box > veh_pose;
     f.n_traj = n_traj;
     f.n_hits = n_hits;
     f.checks = n_hits * s->horizon;
@@ -744,8 +746,12 @@ extern "C" mhc_status mhc_submit(mhc_server *srv, int32_t stream_id, const mhc_s
     auto f = copy_frame(scene);
     f->dst = *dst;
     frame_sizes(&f->scene, dst->first_hit != nullptr, true, *f);
-    // a frame of pedestrians mostly, whose boxes take a quarter of their poses
-    // (vehicles': an eighth), runs without them where it fits a slot only so
+    // The boxes take an eighth of the poses of a vehicle and a quarter of a
+    // pedestrian's, but as much and twice as much of an object of a single
+    // trajectory. A frame whose boxes take more than its vehicles' poses runs
+    // without them where it fits a slot only so: a slot that has room for the
+    // vehicles' poses twice, as their pose and frame blocks took, is enough for
+    // any frame.
     if (f->bytes > srv->slot_usable && f->boxes_optional) frame_sizes(&f->scene, dst->first_hit != nullptr, false, *f);
     f->large = f->checks > srv->cfg.max_checks_per_tick;
     f->stream_id = stream_id;
