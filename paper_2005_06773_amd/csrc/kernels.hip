@@ -717,18 +717,21 @@ struct CheckGG : PrepNone {
             for (int e = 0; e < KQ; ++e) sep |= beyond<KP>(Q->edge[e], px, py);
             return !sep;
         } else {
+            // octagons within 3 m, with boxes and without, edges one by one 113
+            // and 627 us, four together 82 and 366 (all: 84 and 266, but then
+            // the separating axes of the same instance 117 us for 102)
             bool in_q[KQ], in_p[KP];
 #pragma unroll
             for (int v = 0; v < KQ; ++v) in_q[v] = true;
 #pragma unroll
             for (int v = 0; v < KP; ++v) in_p[v] = true;
-#pragma unroll 1
+#pragma unroll 4
             for (int e = 0; e < KP; ++e) {
                 const float nx = P->edge[e].nx, ny = P->edge[e].ny, h = P->edge[e].h;
 #pragma unroll
                 for (int v = 0; v < KQ; ++v) in_q[v] &= fmaf(nx, qx[v], ny * qy[v]) <= h;
             }
-#pragma unroll 1
+#pragma unroll 4
             for (int e = 0; e < KQ; ++e) {
                 const float nx = Q->edge[e].nx, ny = Q->edge[e].ny, h = Q->edge[e].h;
 #pragma unroll
@@ -1243,21 +1246,18 @@ __device__ __forceinline__ void block_tables(K2Lds &w, int slot, const DPair &pr
 // tables: 1 to 2 us each when first touched on a CU), so each of them is made
 // once per block, by waves side by side.
 // A launch may run a part of the plan (strips_before_part): its strips, from
-// strip_lo on, fill full_rows rows and last_row strips of the next.
+// strip_lo on, fill full_rows rows and last_row strips of the next. A wave
+// tests item_rounds rounds of S steps of a unit at a time.
 template <int V, int FAM, bool TL>
 __global__ __launch_bounds__(K2_WG) __attribute__((amdgpu_waves_per_eu(kCollideMinWaves<FAM>))) void k2_collide(
     const DPair *__restrict__ pairs, const DObj *__restrict__ objs, const int64_t *__restrict__ strip0, int n_pairs,
-    int64_t strip_lo, int full_rows, int last_row, int strip_len, int side_shift, const char *__restrict__ poses,
+    int64_t strip_lo, int full_rows, int last_row, int strip_len, int side_shift, int item_rounds,
+    const char *__restrict__ poses,
     int16_t *__restrict__ hits, const unsigned long long *__restrict__ pfix, unsigned long long *__restrict__ qacc,
     unsigned long long *__restrict__ hist, const DPoly *__restrict__ polys)
 {
     constexpr int NW = K2_WG / WAVE;
     const int side = (1 << side_shift) / LEAF;   // leaves to a side of a block
-    // Rounds of S steps that a wave tests at a time: few where the waves of a
-    // workgroup hardly fill (octagons 34 us with 2, 38 with 4), more where
-    // there is work for all of them and an item's set-up counts (stress scene
-    // 332 us with 4, 357 with 2; 64-scene batch 470 and 510).
-    const int item_rounds = strip_len > 1 ? 4 : 2;
     static_assert(NW == K2_SLOTS);
     const int tid = (int)threadIdx.x, lane = tid & (WAVE - 1), wave = uniform(tid / WAVE);
     // per wave: the two polygons of its current polygon pair
@@ -1840,7 +1840,7 @@ static hipError_t launch_k2(const Launch &L, hipStream_t s)
     if (L.n_strips / L.k2_grid >= INT_MAX - K2_WG) return hipErrorInvalidValue;
     hipLaunchKernelGGL((k2_collide<V, FAM, TL>), dim3(L.k2_grid), dim3(K2_WG), 0, s, L.pairs, L.objs, L.strip0, L.n_pairs,
                        lo, (int)((hi - lo) / L.k2_grid), (int)((hi - lo) % L.k2_grid), L.strip_len, L.side_shift,
-                       L.poses, L.hits, L.pfix, L.qacc, L.hist, L.polys);
+                       L.item_rounds, L.poses, L.hits, L.pfix, L.qacc, L.hist, L.polys);
     return hipGetLastError();
 }
 

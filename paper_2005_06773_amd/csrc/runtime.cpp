@@ -519,13 +519,22 @@ static void build_layout_once(const mhc_scene *scenes, int n_scenes, int variant
         n_strips += (int64_t)pr.nbi * pr.nsj;
     }
     L.strip0.push_back(n_strips);
+    // Rounds of S steps that a wave tests at a time: few where the waves of a
+    // workgroup hardly fill (octagons 34 us with 2, 38 with 4), more where
+    // there is work for all of them and an item's set-up counts (stress scene
+    // 332 us with 4, 357 with 2; 64-scene batch 470 and 510). Without boxes
+    // every step of every unit is tested: collision kernel on the stress scene
+    // 21.2 ms with 4, 16.8 with 16; 30 pedestrians in a crowd 293 and 219 us.
+    L.item_rounds = !boxes ? 16 : L.strip_len > 1 ? 4 : 2;
     constexpr int kWaves = K2_WG / WAVE;
     // a strip a wave, but few strips on as many workgroups as there are CUs (a
     // third of the resident ones): what meets in a strip is tested by its
     // workgroup's eight waves together. Whole call on four octagon vehicles of
-    // up to 48 trajectories: 88 us with a strip a wave, 66 so.
+    // up to 48 trajectories: 88 us with a strip a wave, 66 so. Without boxes
+    // everything is tested, by as many workgroups as the GPU holds (11-object
+    // scene, 3520 strips: 67 us on 440 of them, 55 on 768).
     const int64_t want_wg = std::max<int64_t>((n_strips + kWaves - 1) / kWaves,
-                                              std::min<int64_t>(n_strips, max_waves / (3 * kWaves)));
+                                              std::min<int64_t>(n_strips, max_waves / ((boxes ? 3 : 1) * kWaves)));
     L.k2_grid = (int)std::min<int64_t>(want_wg, max_waves > 0 ? std::max(1, max_waves / kWaves) : INT_MAX);
 
     size_t off = 0;
@@ -756,6 +765,7 @@ Launch make_launch(const Layout &L, char *base, const mhc_result *dev_out, bool 
     X.n_pairs = (int)L.pairs.size();
     X.n_strips = L.strip0.back();
     X.strip_len = L.strip_len;
+    X.item_rounds = L.item_rounds;
     X.side_shift = L.side_shift;
     X.n_hits = L.n_hits;
     X.k2_grid = L.k2_grid;
