@@ -65,7 +65,11 @@ static double split_below_units_per_wave(int max_waves) { return max_waves < 102
 // workgroups. Collision kernel on the 11-object scene: 13 us with half a block
 // a wave (sides of 32), 17 with one (16: a second round of looks); octagons,
 // whose tests take 15 times as long, 39 us (mean of four scenes) with two blocks
-// a wave (sides of 16), 54 with eight (sides of 8).
+// a wave (sides of 16), 54 with eight (sides of 8). Sides of 8, whose blocks
+// hold one pair of leaves, pay only while no wave looks twice, except for
+// outlines: plans of sides of 8 and of 16, step of 16 objects of 49 trajectories
+// (0.96 blocks of side 8 a wave) 21 and 25 us, of 12 of 81 (1.2) 21 and 17, of 9
+// of 121 (1.5) 24 and 19; nine vehicles with octagons 45 and 95.
 static double blocks_per_wave(int family) { return family == FAM_POLY ? 2.0 : 0.5; }
 
 // The strip height of traj_at for an n_u x n_w grid: a leaf's positions cover
@@ -486,7 +490,7 @@ static void build_layout_once(const mhc_scene *scenes, int n_scenes, int variant
     auto unit_cols = [&](const DPair &pr) { return (1 << pr.bshift) * kTiles[variant][pr.cls].rj; };
     int least = LEAF;   // no unit is larger than a block
     for (const DPair &pr : L.pairs) least = std::max({least, unit_rows(pr), unit_cols(pr)});
-    for (int side = BLOCK_SIDE; side >= least; side /= 2) {
+    auto cut = [&](int side) {
         n_blocks = 0;
         L.side_shift = 0;
         while ((1 << L.side_shift) < side) ++L.side_shift;
@@ -500,8 +504,12 @@ static void build_layout_once(const mhc_scene *scenes, int n_scenes, int variant
             pr.nbj = (pr.nuj + (1 << pr.block_ucs) - 1) >> pr.block_ucs;
             n_blocks += (int64_t)pr.nbi * pr.nbj;
         }
-        if ((double)n_blocks >= blocks_per_wave(L.family) * max_waves) break;
-    }
+    };
+    int side = BLOCK_SIDE;
+    cut(side);
+    while (side > least && (double)n_blocks < blocks_per_wave(L.family) * max_waves) cut(side /= 2);
+    if (side == LEAF && least < 2 * LEAF && max_waves > 0 && n_blocks > max_waves && L.family != FAM_POLY)
+        cut(side = 2 * LEAF);
     // Large plans: several blocks to a look, whose row's boxes are read once.
     // Neighbouring blocks meet together, so a strip is long only where a wave
     // still gets eight of them. Collision kernel with strips of three blocks
