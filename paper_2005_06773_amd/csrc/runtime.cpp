@@ -535,14 +535,17 @@ static void build_layout_once(const mhc_scene *scenes, int n_scenes, int variant
     // 21.2 ms with 4, 16.8 with 16; 30 pedestrians in a crowd 293 and 219 us.
     L.item_rounds = !boxes ? 16 : L.strip_len > 1 ? 4 : 2;
     constexpr int kWaves = K2_WG / WAVE;
-    // a strip a wave, but few strips on as many workgroups as there are CUs (a
-    // third of the resident ones): what meets in a strip is tested by its
-    // workgroup's eight waves together. Whole call on four octagon vehicles of
-    // up to 48 trajectories: 88 us with a strip a wave, 66 so. Without boxes
-    // everything is tested, by as many workgroups as the GPU holds (11-object
-    // scene, 3520 strips: 67 us on 440 of them, 55 on 768).
+    // a strip a wave, but few strips on as many workgroups as there are CUs,
+    // which hold two workgroups of the outlines' kernel and three of the others:
+    // what meets in a strip is tested by its workgroup's eight waves together.
+    // Whole call on four octagon vehicles of up to 48 trajectories: 88 us with a
+    // strip a wave, 66 on 170 workgroups; step of a queue of six of 25, 240
+    // strips: 28 us on 170, 22 on 240. Without boxes everything is tested, by as
+    // many workgroups as the GPU holds (11-object scene, 3520 strips: 67 us on
+    // 440 of them, 55 on 768).
+    const int per_cu = L.family == FAM_POLY ? 2 : 3;
     const int64_t want_wg = std::max<int64_t>((n_strips + kWaves - 1) / kWaves,
-                                              std::min<int64_t>(n_strips, max_waves / ((boxes ? 3 : 1) * kWaves)));
+                                              std::min<int64_t>(n_strips, max_waves / ((boxes ? per_cu : 1) * kWaves)));
     L.k2_grid = (int)std::min<int64_t>(want_wg, max_waves > 0 ? std::max(1, max_waves / kWaves) : INT_MAX);
 
     size_t off = 0;

@@ -44,3 +44,10 @@ def test_smallest_blocks_only_while_no_wave_looks_twice(mhc, n, side):
     """Plans of 0.96 to 1.5 blocks of side 8 a wave take one round of looks."""
     st, info = mhc.mhc_plan_check(_objects(n, side, False), 0, 6144)
     assert st == mhc.MHC_OK and info["contiguous"] == 0, info
+
+
+@pytest.mark.parametrize("outlines", [False, True])
+def test_few_strips_go_to_as_many_workgroups_as_cus(mhc, outlines):
+    """240 blocks of one pair of leaves each, on 240 workgroups of eight waves."""
+    st, info = mhc.mhc_plan_check(_objects(6, 5, outlines), 0, WAVES[outlines][0])
+    assert st == mhc.MHC_OK and info["n_waves"] == 240 * 8, info
