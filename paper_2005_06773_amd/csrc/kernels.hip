@@ -1011,7 +1011,9 @@ __device__ __forceinline__ bool test_item(const DPair &pr, const char *__restric
 
 // Copies the two polygons of a polygon pair into this wave's LDS slot (each
 // lane a few words), so that their constants reach the tests as vector
-// registers instead of competing for scalar ones.
+// registers instead of competing for scalar ones. Once for all items of a pair
+// that the wave tests one after another: octagons within 3 m 102 us with a copy
+// an item, 100 so.
 __device__ __forceinline__ void stage_polygons(DPoly *slot, const DPoly *__restrict__ polys, const DPair &pr)
 {
     constexpr int words = (int)(sizeof(DPoly) / sizeof(int32_t));
@@ -1265,6 +1267,7 @@ __global__ __launch_bounds__(K2_WG) __attribute__((amdgpu_waves_per_eu(kCollideM
     __shared__ DPoly lds_polys[poly ? 2 * NW : 1];
     __shared__ K2Lds w;
     DPoly *lp = lds_polys + (poly ? 2 * wave : 0);
+    int staged = -1;   // the pair whose polygons are there
     // The counters n_alive and n_units go round three places: one is used now,
     // the next one is emptied before a barrier. That one was last read before
     // the barrier of the use before this one, which every wave has passed.
@@ -1328,7 +1331,10 @@ __global__ __launch_bounds__(K2_WG) __attribute__((amdgpu_waves_per_eu(kCollideM
                         const int word = uniform((int)w.unit[x0 + l]), slot = word >> 16, u = word & 0xFFF;
                         const int4 b = w.alive[k0 + slot];
                         const DPair &pr = pairs[uniform(b.x)];
-                        if (poly && pr.cls >= CLS_GG) stage_polygons(lp, polys, pr);
+                        if (poly && pr.cls >= CLS_GG && staged != uniform(b.x)) {
+                            stage_polygons(lp, polys, pr);
+                            staged = uniform(b.x);
+                        }
                         const int ur = u >> pr.block_ucs, uc = u & ((1 << pr.block_ucs) - 1);
                         const int per = WAVE >> pr.tshift, e = lane & (per - 1), part = lane >> (6 - pr.tshift);
                         const int er = e >> pr.bshift, ec = e & ((1 << pr.bshift) - 1);
