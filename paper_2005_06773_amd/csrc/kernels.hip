@@ -376,8 +376,8 @@ __device__ void one_track_wave(const DObj &o, const double *__restrict__ vals, c
 // longest block for large T, so it is dispatched first), x >= 1 are
 // trajectory blocks of K1_TPB trajectories, one wave each.
 // ONE_TRACK: whether the instance carries the one-track model's scan, whose
-// FP64 state needs far more registers (130 VGPRs against the kinematic
-// instance's); launches without one-track vehicles use the lighter instance,
+// FP64 state needs far more registers (129 VGPRs against the kinematic
+// instance's 79); launches without one-track vehicles use the lighter instance,
 // which also fits beside a running collision kernel on a shared GPU.
 // For time-resolved scenes, trajectory block c also zeroes the c-th stretch
 // of K1_TPB * W * H entries of the object's per-slot q sums. Where the launch
@@ -881,21 +881,22 @@ __device__ __forceinline__ float2 load_pose<float2>(__amdgpu_buffer_rsrc_t r, ui
 // outline test (neighbouring normals turn by at most 135 degrees, interior
 // angles being 45 degrees or more; the cosine of half of it), and a circle by m
 // itself. A step is left out at m > 256 u M (kBoxSlack): 98 u M against 68.
-// kBoxLeast keeps that from underflow: the tests' squares are 0 in FP32 below
-// 1e-22 m and the circle tests then find overlaps that are none, but a gap of
-// 2^-50 m leaves at least 2^-100 between the squares that they compare.
+// A gap of at least kBoxLeast (M counts as 2^16 times that or more) keeps that
+// from underflow: the tests' squares are 0 in FP32 below 1e-22 m and the circle
+// tests then find overlaps that are none, but a gap of 2^-50 m leaves at least
+// 2^-100 between the squares that they compare.
 // Boxes with an infinite side separate nothing, and the comparison is made so
 // that a NaN keeps the step.
 __device__ __forceinline__ float box_size(const float4 a)
 {
-    return fmaxf(fmaxf(fabsf(a.x), fabsf(a.y)), fmaxf(fabsf(a.z), fabsf(a.w)));
+    return fmaxf(fmaxf(fmaxf(fabsf(a.x), fabsf(a.y)), fmaxf(fabsf(a.z), fabsf(a.w))), kBoxLeast / kBoxSlack);
 }
 
 // size: the larger box_size of the two.
 __device__ __forceinline__ bool boxes_meet(const float4 a, const float4 b, float size)
 {
     const float gx = fmaxf(b.x - a.y, a.x - b.y), gy = fmaxf(b.z - a.w, a.z - b.w);
-    return !(fmaxf(gx, gy) > fmaf(size, kBoxSlack, kBoxLeast));
+    return !(fmaxf(gx, gy) > size * kBoxSlack);
 }
 
 // The boxes at this lane's step t of `side` leaves from leaf0 on (past those and
@@ -1249,16 +1250,19 @@ __device__ __forceinline__ void block_tables(K2Lds &w, int slot, const DPair &pr
 // once per block, by waves side by side.
 // A launch may run a part of the plan (strips_before_part): its strips, from
 // strip_lo on, fill full_rows rows and last_row strips of the next. A wave
-// tests item_rounds rounds of S steps of a unit at a time.
+// tests item_rounds rounds of S steps of a unit at a time. The small numbers
+// come in one argument (k2_sizes): as one each they left two of the 80 vector
+// registers of some instances in scratch memory (11-object scene 14.7 us, 14.3
+// so).
 template <int V, int FAM, bool TL>
 __global__ __launch_bounds__(K2_WG) __attribute__((amdgpu_waves_per_eu(kCollideMinWaves<FAM>))) void k2_collide(
     const DPair *__restrict__ pairs, const DObj *__restrict__ objs, const int64_t *__restrict__ strip0, int n_pairs,
-    int64_t strip_lo, int full_rows, int last_row, int strip_len, int side_shift, int item_rounds,
-    const char *__restrict__ poses,
+    int64_t strip_lo, int full_rows, int last_row, uint32_t sizes, const char *__restrict__ poses,
     int16_t *__restrict__ hits, const unsigned long long *__restrict__ pfix, unsigned long long *__restrict__ qacc,
     unsigned long long *__restrict__ hist, const DPoly *__restrict__ polys)
 {
     constexpr int NW = K2_WG / WAVE;
+    const int strip_len = (int)(sizes & 0xFF), side_shift = (int)(sizes >> 8 & 0xFF), item_rounds = (int)(sizes >> 16);
     const int side = (1 << side_shift) / LEAF;   // leaves to a side of a block
     static_assert(NW == K2_SLOTS);
     const int tid = (int)threadIdx.x, lane = tid & (WAVE - 1), wave = uniform(tid / WAVE);
@@ -1833,6 +1837,11 @@ static hipError_t launch_clear_hits(const Launch &L, hipStream_t s)
     return hipGetLastError();
 }
 
+static uint32_t k2_sizes(const Launch &L)
+{
+    return (uint32_t)L.strip_len | (uint32_t)L.side_shift << 8 | (uint32_t)L.item_rounds << 16;
+}
+
 template <int V, int FAM, bool TL>
 static hipError_t launch_k2(const Launch &L, hipStream_t s)
 {
@@ -1845,8 +1854,8 @@ static hipError_t launch_k2(const Launch &L, hipStream_t s)
     if (lo == hi) return hipSuccess;
     if (L.n_strips / L.k2_grid >= INT_MAX - K2_WG) return hipErrorInvalidValue;
     hipLaunchKernelGGL((k2_collide<V, FAM, TL>), dim3(L.k2_grid), dim3(K2_WG), 0, s, L.pairs, L.objs, L.strip0, L.n_pairs,
-                       lo, (int)((hi - lo) / L.k2_grid), (int)((hi - lo) % L.k2_grid), L.strip_len, L.side_shift,
-                       L.item_rounds, L.poses, L.hits, L.pfix, L.qacc, L.hist, L.polys);
+                       lo, (int)((hi - lo) / L.k2_grid), (int)((hi - lo) % L.k2_grid), k2_sizes(L), L.poses, L.hits,
+                       L.pfix, L.qacc, L.hist, L.polys);
     return hipGetLastError();
 }
 
@@ -1905,7 +1914,8 @@ hipError_t launch_collide(const Launch &L, hipStream_t s)
 {
     if (L.n_strips <= 0) return hipSuccess;
     if (L.variant < 0 || L.variant >= N_VARIANTS || L.family < FAM_PLAIN || L.family > FAM_POLY || L.k2_grid < 1 ||
-        L.strip_len < 1 || L.strip_len > MAX_STRIP)
+        L.strip_len < 1 || L.strip_len > MAX_STRIP || L.side_shift < 0 || 1 << L.side_shift > BLOCK_SIDE ||
+        L.item_rounds < 1 || L.item_rounds > WAVE)
         return hipErrorInvalidValue;
     if (L.clear_hits) {
         const hipError_t e = launch_clear_hits(L, s);

@@ -159,7 +159,7 @@ constexpr int K1_TPB = K1_WG / 64; // trajectories per trajectory workgroup (one
 constexpr int LEAF = K1_TPB;      // trajectories of consecutive positions that share a box per step
 // A pose with a coordinate beyond kBoxMax (or not finite) makes its leaf's box
 // infinite; a step is left out of the tests where the boxes lie apart by more
-// than kBoxSlack times their largest coordinate and kBoxLeast.
+// than kBoxSlack times their largest coordinate, and by more than kBoxLeast.
 constexpr float kBoxMax = 1e15f, kBoxSlack = 0x1p-16f, kBoxLeast = 0x1p-50f;
 // q sums are accumulated exactly as integers. EXCLUSIVE reading: p scaled by
 // 2^62 and rounded (sum <= 1). INDEPENDENT reading: -log(1 - p), capped at 64,
