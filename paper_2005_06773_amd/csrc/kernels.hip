@@ -1250,7 +1250,7 @@ __device__ __forceinline__ void block_tables(K2Lds &w, int slot, const DPair &pr
 // once per block, by waves side by side.
 // A launch may run a part of the plan (strips_before_part): its strips, from
 // strip_lo on, fill full_rows rows and last_row strips of the next. A wave
-// tests item_rounds rounds of S steps of a unit at a time. The small numbers
+// tests 2^item_shift rounds of S steps of a unit at a time. The small numbers
 // come in one argument (k2_sizes): as one each they left two of the 80 vector
 // registers of some instances in scratch memory (11-object scene 14.7 us, 14.3
 // so).
@@ -1262,7 +1262,8 @@ __global__ __launch_bounds__(K2_WG) __attribute__((amdgpu_waves_per_eu(kCollideM
     unsigned long long *__restrict__ hist, const DPoly *__restrict__ polys)
 {
     constexpr int NW = K2_WG / WAVE;
-    const int strip_len = (int)(sizes & 0xFF), side_shift = (int)(sizes >> 8 & 0xFF), item_rounds = (int)(sizes >> 16);
+    const int strip_len = (int)(sizes & 0xFF), side_shift = (int)(sizes >> 8 & 0xFF);
+    const int item_shift = (int)(sizes >> 16), item_rounds = 1 << item_shift;
     const int side = (1 << side_shift) / LEAF;   // leaves to a side of a block
     static_assert(NW == K2_SLOTS);
     const int tid = (int)threadIdx.x, lane = tid & (WAVE - 1), wave = uniform(tid / WAVE);
@@ -1326,11 +1327,11 @@ __global__ __launch_bounds__(K2_WG) __attribute__((amdgpu_waves_per_eu(kCollideM
                     const int x = min(x0 + lane, n_units - 1);
                     const int ts = w.unit[x] >> 12 & 7;
                     const int rounds = (__popcll(w.mask[x]) + (1 << ts) - 1) >> ts;
-                    const int upto = scan_add_int(x0 + lane < n_units ? (rounds + item_rounds - 1) / item_rounds : 0);
+                    const int upto = scan_add_int(x0 + lane < n_units ? (rounds + item_rounds - 1) >> item_shift : 0);
                     const int items = __builtin_amdgcn_readlane(upto, WAVE - 1);
                     for (int it = (wave - turn) & (NW - 1); it < items; it += NW) {
                         const int l = __popcll(__ballot(upto <= it));
-                        const int m0 = (it - (l ? __builtin_amdgcn_readlane(upto, l - 1) : 0)) * item_rounds;
+                        const int m0 = (it - (l ? __builtin_amdgcn_readlane(upto, l - 1) : 0)) << item_shift;
                         const unsigned long long mask = w.mask[x0 + l];
                         const int word = uniform((int)w.unit[x0 + l]), slot = word >> 16, u = word & 0xFFF;
                         const int4 b = w.alive[k0 + slot];
@@ -1839,7 +1840,7 @@ static hipError_t launch_clear_hits(const Launch &L, hipStream_t s)
 
 static uint32_t k2_sizes(const Launch &L)
 {
-    return (uint32_t)L.strip_len | (uint32_t)L.side_shift << 8 | (uint32_t)L.item_rounds << 16;
+    return (uint32_t)L.strip_len | (uint32_t)L.side_shift << 8 | (uint32_t)L.item_shift << 16;
 }
 
 template <int V, int FAM, bool TL>
@@ -1915,7 +1916,7 @@ hipError_t launch_collide(const Launch &L, hipStream_t s)
     if (L.n_strips <= 0) return hipSuccess;
     if (L.variant < 0 || L.variant >= N_VARIANTS || L.family < FAM_PLAIN || L.family > FAM_POLY || L.k2_grid < 1 ||
         L.strip_len < 1 || L.strip_len > MAX_STRIP || L.side_shift < 0 || 1 << L.side_shift > BLOCK_SIDE ||
-        L.item_rounds < 1 || L.item_rounds > WAVE)
+        L.item_shift < 0 || 1 << L.item_shift > WAVE)
         return hipErrorInvalidValue;
     if (L.clear_hits) {
         const hipError_t e = launch_clear_hits(L, s);

@@ -235,7 +235,7 @@ struct Launch {
     int n_obj, n_pairs;
     int64_t n_strips, n_hits;     // strips of collision blocks, first-hit entries
     int strip_len;                // blocks of a strip
-    int item_rounds;              // rounds of steps that a wave tests at a time
+    int item_shift;               // log2 of the rounds of steps that a wave tests at a time
     int side_shift;               // log2 of the positions to a side of a block
     int k2_grid;                  // workgroups of the collision kernel
     int k1_x;                     // trajectory kernel grid x: blocks of a row

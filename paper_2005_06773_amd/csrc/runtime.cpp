@@ -533,7 +533,7 @@ static void build_layout_once(const mhc_scene *scenes, int n_scenes, int variant
     // 332 us with 4, 357 with 2; 64-scene batch 470 and 510). Without boxes
     // every step of every unit is tested: collision kernel on the stress scene
     // 21.2 ms with 4, 16.8 with 16; 30 pedestrians in a crowd 293 and 219 us.
-    L.item_rounds = !boxes ? 16 : L.strip_len > 1 ? 4 : 2;
+    L.item_shift = !boxes ? 4 : L.strip_len > 1 ? 2 : 1;
     constexpr int kWaves = K2_WG / WAVE;
     // a strip a wave, but few strips on as many workgroups as there are CUs,
     // which hold two workgroups of the outlines' kernel and three of the others:
@@ -776,7 +776,7 @@ Launch make_launch(const Layout &L, char *base, const mhc_result *dev_out, bool 
     X.n_pairs = (int)L.pairs.size();
     X.n_strips = L.strip0.back();
     X.strip_len = L.strip_len;
-    X.item_rounds = L.item_rounds;
+    X.item_shift = L.item_shift;
     X.side_shift = L.side_shift;
     X.n_hits = L.n_hits;
     X.k2_grid = L.k2_grid;

@@ -43,7 +43,7 @@ struct Layout {
     std::vector<int64_t> strip0;     // [n_pairs+1] first strip of collision blocks of each pair
     int64_t n_units = 0;             // collision units
     int strip_len = 1;               // blocks of a strip
-    int item_rounds = 2;             // rounds of steps that a wave of the collision kernel tests at a time
+    int item_shift = 1;              // log2 of the rounds of steps that a wave of the collision kernel tests at a time
     int side_shift = 0;              // log2 of the positions to a side of a block
     int k2_grid = 0;                 // workgroups of the collision kernel
     std::vector<DPoly> polys;        // polygons of the polygon pairs
