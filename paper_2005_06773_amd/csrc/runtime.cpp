@@ -535,17 +535,19 @@ static void build_layout_once(const mhc_scene *scenes, int n_scenes, int variant
     // 21.2 ms with 4, 16.8 with 16; 30 pedestrians in a crowd 293 and 219 us.
     L.item_shift = !boxes ? 4 : L.strip_len > 1 ? 2 : 1;
     constexpr int kWaves = K2_WG / WAVE;
-    // a strip a wave, but few strips on as many workgroups as there are CUs,
-    // which hold two workgroups of the outlines' kernel and three of the others:
+    // a strip a wave, but few strips on more workgroups, half of those that the
+    // GPU holds (1.5 a CU) and all of them for outlines, whose tests are long:
     // what meets in a strip is tested by its workgroup's eight waves together.
     // Whole call on four octagon vehicles of up to 48 trajectories: 88 us with a
-    // strip a wave, 66 on 170 workgroups; step of a queue of six of 25, 240
-    // strips: 28 us on 170, 22 on 240. Without boxes everything is tested, by as
-    // many workgroups as the GPU holds (11-object scene, 3520 strips: 67 us on
-    // 440 of them, 55 on 768).
-    const int per_cu = L.family == FAM_POLY ? 2 : 3;
+    // strip a wave, 66 on 170 workgroups. Step on one workgroup a CU and so: a
+    // queue of 12 vehicles of 81 trajectories (2376 strips) 26 and 22 us, of six
+    // 19 and 17, of six octagons of 49 (735 strips) 31 and 24; six octagons of
+    // 81 crossing 22.6 and 21.8, twelve of 49 29 and 30. Without boxes everything
+    // is tested, by all of them (11-object scene, 3520 strips: 67 us on 440, 55
+    // on 768).
+    const int held = max_waves / kWaves;
     const int64_t want_wg = std::max<int64_t>((n_strips + kWaves - 1) / kWaves,
-                                              std::min<int64_t>(n_strips, max_waves / ((boxes ? per_cu : 1) * kWaves)));
+                                              std::min<int64_t>(n_strips, !boxes || L.family == FAM_POLY ? held : held / 2));
     L.k2_grid = (int)std::min<int64_t>(want_wg, max_waves > 0 ? std::max(1, max_waves / kWaves) : INT_MAX);
 
     size_t off = 0;

@@ -46,8 +46,10 @@ def test_smallest_blocks_only_while_no_wave_looks_twice(mhc, n, side):
     assert st == mhc.MHC_OK and info["contiguous"] == 0, info
 
 
-@pytest.mark.parametrize("outlines", [False, True])
-def test_few_strips_go_to_as_many_workgroups_as_cus(mhc, outlines):
-    """240 blocks of one pair of leaves each, on 240 workgroups of eight waves."""
-    st, info = mhc.mhc_plan_check(_objects(6, 5, outlines), 0, WAVES[outlines][0])
-    assert st == mhc.MHC_OK and info["n_waves"] == 240 * 8, info
+@pytest.mark.parametrize("n,side,outlines,workgroups", [(6, 5, False, 240), (6, 5, True, 240), (12, 9, False, 384),
+                                                        (8, 7, True, 512), (2, 1, True, 1), (2, 1, False, 1)])
+def test_few_strips_go_to_many_workgroups(mhc, n, side, outlines, workgroups):
+    """One strip a workgroup while there are no more than half of those that
+    the GPU holds, for outlines all of them."""
+    st, info = mhc.mhc_plan_check(_objects(n, side, outlines), 0, WAVES[outlines][0])
+    assert st == mhc.MHC_OK and info["n_waves"] == workgroups * 8, info
